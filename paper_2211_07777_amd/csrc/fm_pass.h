@@ -7,6 +7,7 @@
 namespace fm {
 
 constexpr int kThreads = 256;    // threads per workgroup of every pass kernel
+constexpr int kCurlThreads = 192;  // per-wavefront curl kernel: a wavefront per component
 // Kernel length classes: a compile-time FFT length (> 1), or one of the two
 // runtime-length kernels.  FP64 lines longer than kMaxFastLen64 take the long class.
 constexpr int kRtShort = 0;

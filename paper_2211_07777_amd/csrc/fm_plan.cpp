@@ -510,17 +510,30 @@ bool wave_capable(const fm::PassDesc& d, size_t elem) {
 }
 
 // Values per lane the planner gives a fused pass in the per-wavefront kernel: 8 for
-// three-component lines when their length allows it (three 8-value FP32 lines fit the
-// registers of three waves per SIMD, three 16-value lines need the 256 of two), else
-// 16.  FP64 three-component lines stay on the LDS-tile kernel unless the tuner picks
-// otherwise.
+// three-component lines when their length allows it, else 16.  Three components in FP32
+// (fused pass alone): 0.67 ms with 8 values against 0.73 with 16 at 256^3.
 int default_wave_values(const fm::PassDesc& d, size_t elem) {
   if (d.g.curl && wave_capable(d, elem, 8)) return 8;
   return wave_capable(d, elem, 16) ? 16 : 8;
 }
 
+// FP64 three-component passes run in the per-wavefront kernel by default from this many
+// lines on: 32^3 cells (2112 lines) take 8.6 us there and 8.5 in the LDS-tile kernel, 64^3
+// (8320 lines) 21 and 29, 128^3 139 and 200.
+constexpr int64_t kCurlWaveLines64 = 4096;
+// Three-component tiles of one group of lines below this many lines (many small workgroups
+// fill the chip: FP32 64^3, 12.9 us against 14.5 with two groups), of four groups above
+// (256^3: 0.67 against 0.68 ms, 512^3: 5.6 against 6.0 ms).
+constexpr int64_t kCurlWideLines = 65536;
+
 size_t wave_lds(int B, int M, size_t elem) {
   return round256((size_t)B * fm::fft_line_stride(M) * 2 * elem);
+}
+
+// FFT lines a fused pass of B lines per workgroup holds in LDS at once: all of them, or
+// for three components those of one group of wave_lines (the workgroup walks the groups).
+int wave_fused_lds_lines(const fm::PassDesc& d, int B, int E) {
+  return d.g.curl ? 3 * fm::wave_lines(d.M, E) : B;
 }
 
 // Pass d in the per-wavefront kernel with E values per lane and W (1, 2 or 4) wavefronts
@@ -532,7 +545,7 @@ bool set_wave(fm::PassDesc* d, size_t elem, int W, int comp_tiles, int E) {
   if (!d->fused && W != 4) return false;
   const int F = W * fm::wave_lines(d->M, E);  // FFT lines per workgroup
   const int B = d->fused ? F : F * wave_plain_pk(*d);
-  const size_t lds = wave_lds(F, d->M, elem);
+  const size_t lds = wave_lds(d->fused ? wave_fused_lds_lines(*d, B, E) : F, d->M, elem);
   if (lds > (size_t)fm::kMaxLds) return false;
   if (!d->fused && (int64_t)B * d->in_n > (int64_t)fm::kThreads * wave_plain_u(*d, E)) return false;
   size_t total = lds;
@@ -684,7 +697,7 @@ int make_tables_and_green(fm_plan_s* p, hipStream_t st, bool deferred) {
     }
     if (planned) p->pass[i].stw = p->stw[M];
   }
-  for (int i = 0; i < fm_plan_s::kPasses; ++i) p->stw_plan[i] = p->pass[i].stw;
+  for (int i = 0; i < fm_plan_s::kPasses; ++i) p->stw_plan[i] = p->long_rt[i] ? nullptr : p->pass[i].stw;
 
   // stage twiddles of the per-wavefront kernels (a pass may run there, now or after
   // tuning), one table per length and values per lane
@@ -998,7 +1011,8 @@ bool wave_in_bounds(const fm::PassDesc& d, int64_t in_size, int64_t out_size, si
   if (d.g.curl && d.ncomp != 3) return false;
   if (comps > 1 && (d.in_s_comp < in_size || d.out_s_comp < out_size)) return false;
   if (d.g.fold_line != d.M || d.g.F_line < d.M / 2 + 1) return false;
-  if ((size_t)d.lds_bytes < wave_lds(d.B, d.M, elem) || d.lds_bytes > fm::kMaxLds) return false;
+  if ((size_t)d.lds_bytes < wave_lds(wave_fused_lds_lines(d, d.B, E), d.M, elem) || d.lds_bytes > fm::kMaxLds)
+    return false;
   const int nbt = (d.nb + d.B - 1) / d.B;
   return d.tiles == nbt * d.nc * (d.g.curl ? 1 : d.ncomp);
 }
@@ -1469,12 +1483,16 @@ int build_plan(fm_plan_s* p) {
     if (rc2) return rc2;
     d.tiles = ((d.nb + d.B - 1) / d.B) * d.nc * (fused_curl ? 1 : d.ncomp);
     set_magics(&d);
-    if (i == 2 && wave_capable(d, p->elem) && !(fused_curl && p->elem == 8)) {
+    fm::PassDesc wd = d;  // the per-wavefront kernels have the compile-time length class
+    wd.long_rt = 0;
+    const int64_t lines = (int64_t)d.nb * d.nc;
+    if (i == 2 && wave_capable(wd, p->elem) && !(fused_curl && p->elem == 8 && lines < kCurlWaveLines64)) {
       // the per-wavefront kernel, with the most wavefronts per workgroup whose LDS stays
       // within the preferred size
-      const int E = default_wave_values(d, p->elem);
+      const int E = default_wave_values(wd, p->elem);
       for (const int W : {4, 2, 1}) {
-        fm::PassDesc w = d;
+        if (fused_curl && W > 1 && lines < kCurlWideLines) continue;
+        fm::PassDesc w = wd;
         if (set_wave(&w, p->elem, W, fused_curl ? 1 : d.ncomp, E) && w.lds_bytes <= fm::kSoftLds) {
           d = w;
           break;

@@ -12,7 +12,8 @@
 // last stage leaves the outputs in natural order in the lane layout above.  Nothing is
 // shared between wavefronts, so there is no workgroup barrier: the LDS exchanges are
 // ordered within the wave only.  L = 64 / P lines share a wavefront, W wavefronts a
-// workgroup (one tile of W * L lines).
+// workgroup (one tile of W * L lines).  The three-component (curl) form gives each
+// component its own wavefront (wave_curl_tile).
 #pragma once
 #include "fm_device.h"
 
@@ -33,6 +34,40 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The same pointer (uniform) or lane index (per lane), whose value the compiler cannot
+// connect with the original.  The forward and the inverse transform read the same twiddles,
+// and the groups of a tile the same tables: kept in registers from one to the other, those
+// loads and their addresses held up to 5 E registers across the whole tile, where reading
+// them again costs cache hits that hide behind the exchanges.
+template <class P>
+__device__ __forceinline__ P unlinked(P p) {
+#ifdef __HIP_DEVICE_COMPILE__
+  asm volatile("" : "+s"(p));
+#endif
+  return p;
+}
+__device__ __forceinline__ int unlinked_lane(int j) {
+#ifdef __HIP_DEVICE_COMPILE__
+  asm volatile("" : "+v"(j));
+#endif
+  return j;
+}
+
+// Nothing is scheduled across: holds a phase of an unrolled loop to its registers.
+__device__ __forceinline__ void sched_fence() {
+#ifdef __HIP_DEVICE_COMPILE__
+  __builtin_amdgcn_sched_barrier(0);
+#endif
+}
+
+// Folded spectral index min(k, M - k) of point k = j + P m of a line (j < P, so k < M / 2
+// for the first half of a lane's points): one of two addresses plus a constant.
+template <int M, int E>
+__device__ __forceinline__ int wave_fold(int j, int m) {
+  constexpr int P = M / E;
+  return m < E / 2 ? j + P * m : (M - P * m) - j;
 }
 
 // Stage s of the wave FFT (sign S) and all later stages.  Before the stage, v[i R + r]
@@ -98,14 +133,13 @@ __device__ __forceinline__ void wave_stages(cpx<T> (&v)[E], int j, cpx<T>* buf, 
   }
 }
 
-// One tile of the fused pass: W wavefronts of L lines each.  KIND is K_F_C2C (Poisson:
-// times the Green's spectrum) or K_F_CURL (three components per line: u = G i w x f).
-template <typename T, int M, int KIND, int EV>
+// One tile of the scalar fused pass (Poisson: times the Green's spectrum): W wavefronts of
+// L lines each.
+template <typename T, int M, int EV>
 __device__ __forceinline__ void wave_tile(const PassDesc& d, const void* in, void* out, char* smem,
                                           int tile) {
   using WS = WaveShape<T, M, EV>;
   constexpr int E = WS::E, P = WS::P, L = WS::L;
-  constexpr int NCL = KIND == K_F_CURL ? 3 : 1;
   const int wave = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63;
   const int j = lane % P;
   const int l = wave * L + lane / P;  // line of the tile
@@ -114,99 +148,177 @@ __device__ __forceinline__ void wave_tile(const PassDesc& d, const void* in, voi
   cpx<T>* buf = reinterpret_cast<cpx<T>*>(smem) + (size_t)(wave * L + lane / P) * fft_line_stride(M);
   const GTab<T> tw = gptr<cpx<T>>(E == 16 ? d.wtw : (E == 8 ? d.wtw8 : d.wtw32));
   const int b = ti.b0 + l;
-  const int comp0 = NCL == 3 ? 0 : ti.comp;
-  const int64_t line_off = (int64_t)ti.c * d.in_s_c + (int64_t)b * d.in_s_b;
 
   // the Green's row of the line, folded: G[fold(k)] for k = j + P m (coalesced; the upper
-  // half of a row reads the lower half again, from cache)
+  // half of a row reads the lower half again, from cache), loaded ahead of the transforms
+  // (its latency hides behind them)
   const auto* G = gptr<T>(d.g.G);
   const int64_t grow = ((int64_t)fold_index(ti.c, d.g.fold_c) * d.g.F_b + fold_index(b, d.g.fold_b)) *
                        (int64_t)d.g.F_line;
-  // Poisson: the row is loaded ahead of the transforms (its latency hides behind them);
-  // the curl loads it after its three forward transforms, when registers are free
   T g[E];
-  if constexpr (KIND != K_F_CURL) {
 #pragma unroll
-    for (int m = 0; m < E; ++m) g[m] = G[grow + fold_index(j + P * m, d.g.fold_line)];
-  }
+  for (int m = 0; m < E; ++m) g[m] = G[grow + fold_index(j + P * m, d.g.fold_line)];
 
-  cpx<T> v[NCL][E];
+  cpx<T> v[E];
+  const auto* src = gptr<cpx<T>>(in) + (int64_t)ti.comp * d.in_s_comp + (int64_t)ti.c * d.in_s_c +
+                    (int64_t)b * d.in_s_b;
 #pragma unroll
-  for (int q = 0; q < NCL; ++q) {
-    const auto* src = gptr<cpx<T>>(in) + (int64_t)(comp0 + q) * d.in_s_comp + line_off;
+  for (int m = 0; m < E; ++m) {
+    const int n = j + P * m;
+    v[m] = cpx<T>{T(0), T(0)};
+    if (n < d.n_data) {
+      const auto& z = src[n];
+      v[m] = cpx<T>{z.x, z.y};
+    }
+  }
+  wave_stages<T, M, E, 0, -1>(v, j, buf, tw);
+#pragma unroll
+  for (int m = 0; m < E; ++m) v[m] = {v[m].x * g[m], v[m].y * g[m]};
+  wave_stages<T, M, E, 0, +1>(v, j, buf, tw);
+  auto* dst = (__attribute__((address_space(1))) cpx<T>*)(out) + (int64_t)ti.comp * d.out_s_comp +
+              (int64_t)ti.c * d.out_s_c + (int64_t)b * d.out_s_b;
+#pragma unroll
+  for (int m = 0; m < E; ++m) {
+    const int n = j + P * m;
+    if (n < d.out_n) {
+      dst[n].x = v[m].x;
+      dst[n].y = v[m].y;
+    }
+  }
+}
+
+// One tile of the three-component fused pass (u = G i w x f): three wavefronts, wavefront
+// q transforms component q of L lines at a time and walks the tile's groups of L lines.
+// Component q of the product needs only the two other components of f, so each wavefront
+// leaves its spectrum in its LDS lines, and after a workgroup barrier reads the two others
+// at its own points; a second barrier frees the lines for the inverse's exchanges.
+// A wavefront thus holds one line's E values instead of three lines': 128 registers and
+// four waves per SIMD in FP32 at 1024 points, where one wavefront per line with its three
+// components took 304 and ran one.  It is bound by the latency of its phases (HBM loads,
+// exchanges, two barriers): requesting the next group's input during the inverse took
+// registers from the occupancy and ran 10 % slower in FP32 and 2.4 times in FP64.
+// Measured, one component set of 512^3 (13.45 GB in FP32): 5.61 ms (2.40 TB/s) against
+// 8.77 ms, FP64 10.84 ms against 18.2 ms; 256^3 FP64: 1.12 ms against 1.55 ms.
+template <typename T, int M, int EV>
+__device__ __forceinline__ void wave_curl_tile(const PassDesc& d, const void* in, void* out, char* smem,
+                                               int tile) {
+  using WS = WaveShape<T, M, EV>;
+  constexpr int E = WS::E, P = WS::P, L = WS::L;
+  constexpr int LS = fft_line_stride(M);
+  const int q = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63;
+  const int qa = q == 2 ? 0 : q + 1, qb = q == 0 ? 2 : q - 1;  // (q + 1) mod 3, (q + 2) mod 3
+  const int j0 = lane % P, sub = lane / P;
+  const TileIdx ti = tile_index(d, tile);
+  cpx<T>* lines = reinterpret_cast<cpx<T>*>(smem);
+  cpx<T>* buf = lines + (size_t)(q * L + sub) * LS;
+  const cpx<T>* bufa = lines + (size_t)(qa * L + sub) * LS;
+  const cpx<T>* bufb = lines + (size_t)(qb * L + sub) * LS;
+  const GTab<T> tw = gptr<cpx<T>>(E == 16 ? d.wtw : (E == 8 ? d.wtw8 : d.wtw32));
+  const auto* G = gptr<T>(d.g.G);
+  const auto* wline = gptr<T>(d.g.dtab_line);
+  const int64_t growc = (int64_t)fold_index(ti.c, d.g.fold_c) * d.g.F_b;
+  T wc, mc;
+  curl_factor<T>(d.g.csym, curl_wave<T>(ti.c, d.g.dtab_c), wc, mc);
+  for (int g0 = 0; g0 < ti.nl; g0 += L) {  // uniform over the workgroup
+    const int j = unlinked_lane(j0);
+    const int l = g0 + sub;
+    const bool live = l < ti.nl;
+    const int b = ti.b0 + (live ? l : ti.nl - 1);  // idle lanes read the tile's last line
+    const auto* src = gptr<cpx<T>>(in) + (int64_t)q * d.in_s_comp + (int64_t)ti.c * d.in_s_c +
+                      (int64_t)b * d.in_s_b;
+    cpx<T> v[E];
 #pragma unroll
     for (int m = 0; m < E; ++m) {
       const int n = j + P * m;
-      v[q][m] = cpx<T>{T(0), T(0)};
+      v[m] = cpx<T>{T(0), T(0)};
       if (n < d.n_data) {
         const auto& z = src[n];
-        v[q][m] = cpx<T>{z.x, z.y};
+        v[m] = cpx<T>{z.x, z.y};
       }
     }
-    wave_stages<T, M, E, 0, -1>(v[q], j, buf, tw);
-  }
-  if constexpr (KIND == K_F_CURL) {
+    wave_stages<T, M, E, 0, -1>(v, j, buf, unlinked(tw));
+    wave_lds_sync();  // the last exchange's reads are done
 #pragma unroll
-    for (int m = 0; m < E; ++m) g[m] = G[grow + fold_index(j + P * m, d.g.fold_line)];
-    T wc, mc, wb, mb;
-    curl_factor<T>(d.g.csym, curl_wave<T>(ti.c, d.g.dtab_c), wc, mc);
-    if constexpr (sizeof(T) == 8 && E == 16) {
-      // no symmetric b direction in this instance (its registers are full; the planner
-      // keeps such passes off it)
-      wb = curl_wave<T>(b, d.g.dtab_b);
-      mb = T(0);
-    } else {
-      curl_factor<T>(d.g.csym_b, curl_wave<T>(b, d.g.dtab_b), wb, mb);
-    }
-#pragma unroll
-    for (int m = 0; m < E; ++m) {
-      const T wl = curl_wave<T>(j + P * m, d.g.dtab_line);
-      const T wx = d.g.axis_line == 0 ? wl : (d.g.axis_b == 0 ? wb : wc);
-      const T wy = d.g.axis_line == 1 ? wl : (d.g.axis_b == 1 ? wb : wc);
-      const T wz = d.g.axis_line == 2 ? wl : (d.g.axis_b == 2 ? wb : wc);
-      curl_point<T>(g[m], wx, wy, wz, d.g.axis_c, mc, d.g.axis_b, mb, v[0][m], v[1][m], v[2][m]);
-    }
-  } else {
-#pragma unroll
-    for (int m = 0; m < E; ++m) v[0][m] = {v[0][m].x * g[m], v[0][m].y * g[m]};
-  }
-#pragma unroll
-  for (int q = 0; q < NCL; ++q) {
-    wave_stages<T, M, E, 0, +1>(v[q], j, buf, tw);
-    auto* dst = (__attribute__((address_space(1))) cpx<T>*)(out) +
-                (int64_t)(comp0 + q) * d.out_s_comp + (int64_t)ti.c * d.out_s_c + (int64_t)b * d.out_s_b;
+    for (int m = 0; m < E; ++m) buf[pad16(j + P * m)] = v[m];
+    // the Green's row and the factors of the two directions a, b of the product, on their
+    // way while the wavefronts meet: direction axis_line's factor varies along the line,
+    // the two others are the same for the whole line
+    const int64_t grow = (growc + fold_index(b, d.g.fold_b)) * (int64_t)d.g.F_line;
+    T wb, mb;
+    curl_factor<T>(d.g.csym_b, curl_wave<T>(b, d.g.dtab_b), wb, mb);
+    auto fixed = [&](int a, T& re, T& im) {
+      re = a == d.g.axis_b ? wb : (a == d.g.axis_c ? wc : T(0));
+      im = a == d.g.axis_b ? mb : (a == d.g.axis_c ? mc : T(0));
+    };
+    T are, aim, bre, bim;
+    fixed(qa, are, aim);
+    fixed(qb, bre, bim);
+    const bool la = qa == d.g.axis_line, lb = qb == d.g.axis_line;  // uniform over the wavefront
+    const bool imag = d.g.csym != 0 || d.g.csym_b != 0;             // uniform over the grid
+    T g[E], wl[E];
 #pragma unroll
     for (int m = 0; m < E; ++m) {
-      const int n = j + P * m;
-      if (n < d.out_n) {
-        dst[n].x = v[q][m].x;
-        dst[n].y = v[q][m].y;
+      g[m] = G[grow + wave_fold<M, E>(j, m)];
+      wl[m] = wline[j + P * m];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < E; ++m) {
+      if (m % 4 == 0) sched_fence();  // four points' values in registers at a time
+      const int k = j + P * m;
+      const T xa = la ? wl[m] : are, xb = lb ? wl[m] : bre;
+      // i g (w_a f_b - w_b f_a)
+      const cpx<T> fa = bufa[pad16(k)], fb = bufb[pad16(k)];
+      cpx<T> z = {xa * fb.x - xb * fa.x, xa * fb.y - xb * fa.y};
+      if (imag) {
+        z.x += bim * fa.y - aim * fb.y;
+        z.y += aim * fb.x - bim * fa.x;
+      }
+      v[m] = {-g[m] * z.y, g[m] * z.x};
+    }
+    sched_fence();
+    __syncthreads();  // every wavefront has read the spectra
+    wave_stages<T, M, E, 0, +1>(v, unlinked_lane(j), buf, unlinked(tw));
+    if (live) {
+      auto* dst = (__attribute__((address_space(1))) cpx<T>*)(out) + (int64_t)q * d.out_s_comp +
+                  (int64_t)ti.c * d.out_s_c + (int64_t)b * d.out_s_b;
+#pragma unroll
+      for (int m = 0; m < E; ++m) {
+        const int n = j + P * m;
+        if (n < d.out_n) {
+          dst[n].x = v[m].x;
+          dst[n].y = v[m].y;
+        }
       }
     }
+    wave_lds_sync();  // the inverse's exchange reads are done before the next group's writes
   }
 }
 
 // Tiles in the XCD-aware order of the other pass kernels; a grid of one workgroup per
 // tile gives each workgroup one or two tiles.
-// Occupancy targets of the three-component (curl) kernels: 16 values per lane (1024-point
-// lines) keep one wave per SIMD, where FP32 fits without spilling (two waves spill some
-// 300 bytes per lane and ran 20 % slower on the 512^3 Biot-Savart pass) and FP64 takes the
-// 512 architectural and accumulation registers; 8 FP32 values fit the 168 of three (FP64
-// would spill there and keeps the compiler's choice).
+// Occupancy targets (waves per SIMD) that the curl kernels fit: FP32 four with 16 values per
+// lane (at most 5 dwords spilled at 1024 points) and six with 8, FP64 two and four.
 template <typename T, int KIND, int E>
 constexpr int wave_min_waves() {
-  return KIND == K_F_CURL ? (E == 16 ? 1 : (sizeof(T) == 4 ? 3 : 1)) : 1;
+  return KIND != K_F_CURL ? 1 : (sizeof(T) == 4 ? (E == 16 ? 4 : 6) : (E == 16 ? 2 : 4));
 }
 
 template <typename T, int M, int KIND, int E>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(wave_min_waves<T, KIND, E>())))
+__global__ __launch_bounds__(KIND == K_F_CURL ? kCurlThreads : kThreads)
+__attribute__((amdgpu_waves_per_eu(wave_min_waves<T, KIND, E>())))
 void wave_pass_kernel(const PassDesc* __restrict__ dp, const void* in, void* out) {
   extern __shared__ __align__(16) char smem[];
   const PassDesc& d = *dp;
   for (int k = 0;; ++k) {
     const int tile = xcd_tile(blockIdx.x, gridDim.x, k, d.tiles);
     if (tile < 0) return;
-    wave_tile<T, M, KIND, E>(d, in, out, smem, tile);
+    if constexpr (KIND == K_F_CURL) {
+      if (k > 0) __syncthreads();
+      wave_curl_tile<T, M, E>(d, in, out, smem, tile);
+    } else {
+      wave_tile<T, M, E>(d, in, out, smem, tile);
+    }
   }
 }
 
