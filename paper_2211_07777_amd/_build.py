@@ -20,6 +20,9 @@ FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # keep the compiler from forming packed FP32 instructions
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # no calls in device code: a called function too large for branch instructions lost its
+    # return address to its own long branches (see fm_device.h, plain_compute)
+    "-mllvm", "-amdgpu-function-calls=false",
 ]
 LENGTHS = [0, 32, 48, 64, 96, 128, 192, 256, 384, 512, 768, 1024, 2048, 4096]
 PRECISIONS = ["float", "double"]

@@ -846,10 +846,17 @@ __device__ __forceinline__ void plain_store(const PassDesc& d, void* out, const 
   }
 }
 
+// The tile functions are inlined into their kernels by force.  Called as functions, the
+// larger ones exceed the reach of a branch instruction, and the compiler then built the
+// long branches in the register pair s[30:31], which in a function without spills still
+// held the return address: the function ended by jumping into its own middle, with
+// registers that meant something else (10 such branches in the two functions of the FP32
+// batched kernel of the runtime lengths).  A kernel has no return address.
+//
 // DIRECT: forward complex or real-to-complex lines read by the first FFT stage straight
 // from contiguous input lines at gin (the tile's first line) instead of the LDS raw tile.
 template <typename T, int MC, int KIND, bool DIRECT = false, class P>
-__device__ void plain_compute(const PassDesc& d, void* out, const TileIdx& ti, char* smem,
+__device__ __forceinline__ void plain_compute(const PassDesc& d, void* out, const TileIdx& ti, char* smem,
                               const Tabs<P>& tb, const void* gin = nullptr) {
   const int gather = KIND == K_ANY ? d.gather : gather_of(KIND);
   const int scatter = KIND == K_ANY ? d.scatter : scatter_of(KIND);
@@ -934,7 +941,7 @@ __device__ void plain_compute(const PassDesc& d, void* out, const TileIdx& ti, c
 // Fused pass 3 on one tile: forward FFT, spectral multiply, inverse FFT.
 // ---------------------------------------------------------------------------------
 template <typename T, int MC, int KIND, class P>
-__device__ void fused_compute(const PassDesc& d, void* out, const TileIdx& ti, char* smem,
+__device__ __forceinline__ void fused_compute(const PassDesc& d, void* out, const TileIdx& ti, char* smem,
                               const Tabs<P>& tb) {
   const int gather = KIND == K_ANY ? d.gather : gather_of(KIND);
   const bool curl = KIND == K_ANY ? (d.g.curl != 0) : (KIND == K_F_CURL);
@@ -1300,27 +1307,27 @@ __device__ __forceinline__ void compute(const PassDesc& d, void* out, const Tile
 
 // One tile, no pipelining (batched launches: the kind is read from the descriptor).
 template <typename T, int MC, typename E, int NCL>
-__device__ __forceinline__ void run_tile_e(const PassDesc& d, const void* in, void* out, int tile,
-                                           char* smem) {
+__device__ __forceinline__ void load_tile_any(const PassDesc& d, const void* in, const TileIdx& ti,
+                                              char* smem) {
   constexpr int U = StageCount<T, E, NCL, MC>::U;
   constexpr int UG = green_stage<T, MC, K_ANY>();
   RegStage<T, E, U * NCL> v;
   GreenStage<T, UG> gs;
-  const TileIdx ti = tile_index(d, tile);
   fetch<U, NCL, (MC <= 1), E>(v, d, in, ti);
   if (d.fused) fetch_green<T, UG>(gs, d, ti);
   commit<U, NCL, E>(v, d, ti, smem);
   if (d.fused) commit_green<T, UG>(gs, d, ti, smem);
-  __syncthreads();
-  compute<T, MC, K_ANY>(d, out, ti, smem, global_tabs<T>(d));
 }
 
 template <typename T, int MC>
 __device__ __forceinline__ void run_tile(const PassDesc& d, const void* in, void* out, int tile,
                                          char* smem) {
-  if (d.fused && d.g.curl) run_tile_e<T, MC, cpx<T>, 3>(d, in, out, tile, smem);
-  else if (d.in_cplx) run_tile_e<T, MC, cpx<T>, 1>(d, in, out, tile, smem);
-  else run_tile_e<T, MC, T, 1>(d, in, out, tile, smem);
+  const TileIdx ti = tile_index(d, tile);
+  if (d.fused && d.g.curl) load_tile_any<T, MC, cpx<T>, 3>(d, in, ti, smem);
+  else if (d.in_cplx) load_tile_any<T, MC, cpx<T>, 1>(d, in, ti, smem);
+  else load_tile_any<T, MC, T, 1>(d, in, ti, smem);
+  __syncthreads();
+  compute<T, MC, K_ANY>(d, out, ti, smem, global_tabs<T>(d));
 }
 
 // XCD-aware order of the tiles.  Workgroups are dispatched to the 8 XCDs round-robin
