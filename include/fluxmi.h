@@ -343,7 +343,8 @@ typedef struct {
   int order[3];         /* transform order, as axis indices (0 x, 1 y, 2 z)           */
   int axis_class[3];    /* per axis x, y, z: 0 P, 1 EE, 2 OO, 3 EO, 4 OE, 5 UU, 6 EU,
                            7 OU, 8 UE, 9 UO (left face first)                          */
-  int fft_len[3];       /* FFT length used along each axis                           */
+  int fft_len[3];       /* period of each axis in points: the DFT length, or that of the
+                           symmetric extension of a real-to-real axis                 */
   int spec_len[3];      /* extent of each axis after its forward transform           */
   int green_dims[3];    /* Green table extents, in transform order                   */
   size_t workspace_bytes;

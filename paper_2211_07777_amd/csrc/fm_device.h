@@ -307,58 +307,9 @@ __device__ __forceinline__ uint32_t fdiv(uint32_t n, uint64_t mag) {
 // One Stockham radix-R stage over F lines of length M held in LDS (line stride ls).
 // Butterfly t of a line reads x[t + r M/R], twiddles by W_{Ns R}^{(t mod Ns) r}, and
 // writes to (t - t mod Ns) R + t mod Ns + q Ns.  The first stage reads through
-// `load` (the gather), later stages read LDS.  Runtime-length form: twiddles from the
-// 4M table; compile-time form: M, R, Ns are constants and twiddles come from the
-// per-stage table (contiguous per butterfly).
+// `load` (the gather), later stages read LDS.  M, R, Ns are constants and twiddles come
+// from the per-stage table (contiguous per butterfly).
 // ---------------------------------------------------------------------------------
-template <typename T, int EL, int R, int S, class P, class Load>
-__device__ __forceinline__ void fft_stage(cpx<T>* buf, int ls, int F, int M, int Ns, P tw,
-                                          Load& load) {
-  constexpr int NB = (EL + R - 1) / R;
-  cpx<T> v[NB][R];
-  int lin[NB], tt[NB];
-  const int MR = M / R;
-  const int total = F * MR;
-  const int twstep = 4 * (MR / Ns);  // 4M table: W_{Ns R}^e = tw[4 e M / (Ns R)]
-#pragma unroll
-  for (int i = 0; i < NB; ++i) {
-    const int u = (int)threadIdx.x + i * kThreads;
-    lin[i] = -1;
-    tt[i] = 0;
-    if (u < total) {
-      const int line = u / MR;
-      const int t = u - line * MR;
-      const int k = t % Ns;
-      lin[i] = line;
-      tt[i] = t;
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        cpx<T> a = load(line, t + r * MR);
-        if (r > 0 && k > 0) {
-          cpx<T> w = twid<T>(tw, k * r * twstep);
-          if (S > 0) w.y = -w.y;
-          a = cmul(a, w);
-        }
-        v[i][r] = a;
-      }
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < NB; ++i) {
-    if (lin[i] >= 0) {
-      SmallDft<R, S, T>::run(v[i]);
-      const int t = tt[i];
-      const int k = t % Ns;
-      const int base = (t - k) * R + k;
-      cpx<T>* row = buf + lin[i] * ls;
-#pragma unroll
-      for (int q = 0; q < R; ++q) row[pad16(base + q * Ns)] = v[i][q];
-    }
-  }
-  __syncthreads();
-}
-
 // Destination of the last stage's outputs: NoSink writes them to LDS (natural order);
 // any other sink is called as sink(line, slot, value) for the kept slots instead.
 struct NoSink {};
@@ -430,40 +381,14 @@ __device__ __forceinline__ void stages_ct(cpx<T>* buf, int ls, int F, P stw, Loa
   }
 }
 
-template <typename T, int EL, int S, class P, class Load>
-__device__ __forceinline__ void fft_stage_dispatch(int R, cpx<T>* buf, int ls, int F, int M,
-                                                   int Ns, P tw, Load& load) {
-  switch (R) {
-    case 8: fft_stage<T, EL, 8, S>(buf, ls, F, M, Ns, tw, load); break;
-    case 4: fft_stage<T, EL, 4, S>(buf, ls, F, M, Ns, tw, load); break;
-    case 2: fft_stage<T, EL, 2, S>(buf, ls, F, M, Ns, tw, load); break;
-    case 3: fft_stage<T, EL, 3, S>(buf, ls, F, M, Ns, tw, load); break;
-    case 5: fft_stage<T, EL, 5, S>(buf, ls, F, M, Ns, tw, load); break;
-    case 7: fft_stage<T, EL, 7, S>(buf, ls, F, M, Ns, tw, load); break;
-    default: break;
-  }
-}
-
-// Full FFT of F lines; result in buf in natural order.  MC = compile-time length or 0.
-// Compile-time lengths write only the first `keep` outputs of each line (the rest are
-// cropped by the caller and never read).
+// Full FFT of F lines of length MC; result in buf in natural order.  Only the first
+// `keep` outputs of each line are written (the rest are cropped by the caller and never
+// read).
 template <typename T, int MC, int S, class P, class Load>
 __device__ __forceinline__ void fft_lines(cpx<T>* buf, int ls, int F, const PassDesc& d, P stw,
                                           Load& load0, int keep = 1 << 30) {
-  if constexpr (MC > 1) {
-    stages_ct<T, MC, S, 0, 1>(buf, ls, F, stw, load0, keep, NoSink{});
-  } else {
-    constexpr int EL = elems_per_thread((int)sizeof(T), MC);
-    const GTab<T> tw = gptr<cpx<T>>(d.tw);  // runtime lengths: the 4M table in global memory
-    auto lds = [buf, ls](int line, int idx) { return buf[line * ls + pad16(idx)]; };
-    int Ns = 1;
-    for (int s = 0; s < d.nstages; ++s) {
-      const int R = d.radix[s];
-      if (s == 0) fft_stage_dispatch<T, EL, S>(R, buf, ls, F, d.M, Ns, tw, load0);
-      else fft_stage_dispatch<T, EL, S>(R, buf, ls, F, d.M, Ns, tw, lds);
-      Ns *= R;
-    }
-  }
+  (void)d;
+  stages_ct<T, MC, S, 0, 1>(buf, ls, F, stw, load0, keep, NoSink{});
 }
 
 // Twiddle tables seen by a tile: in LDS for persistent kernels (copied once per
@@ -1197,8 +1122,8 @@ struct RegStage<T, cpx<T>, N> {
 
 // Global -> registers.  Addresses are a uniform 64-bit base per component plus a 32-bit
 // byte offset per element; the planner sends tiles that span 4 GiB or more to the
-// runtime-length kernels (OFF64), which use 64-bit offsets.
-template <int U, int NCL, bool OFF64, typename E, class Stage>
+// runtime-length kernel, which uses 64-bit offsets.
+template <int U, int NCL, typename E, class Stage>
 __device__ __forceinline__ void fetch(Stage& v, const PassDesc& d, const void* in, const TileIdx& ti) {
   const TileWalk w = in_walk(d, ti);
   const int comp0 = NCL == 3 ? 0 : ti.comp;
@@ -1211,14 +1136,9 @@ __device__ __forceinline__ void fetch(Stage& v, const PassDesc& d, const void* i
     for (int u = 0; u < U; ++u) {
       int l, i;
       if (w.at((int)threadIdx.x + u * kThreads, l, i)) {
-        if constexpr (OFF64) {
-          const int64_t off = ((int64_t)l * d.in_s_b + (int64_t)i * d.in_s_line) * (int64_t)sizeof(E);
-          v.set(q * U + u, *reinterpret_cast<const E*>(base + off));
-        } else {
-          const uint32_t off = ((uint32_t)l * (uint32_t)d.in_s_b + (uint32_t)i * (uint32_t)d.in_s_line) *
-                               (uint32_t)sizeof(E);
-          v.set(q * U + u, *reinterpret_cast<const E*>(base + off));
-        }
+        const uint32_t off = ((uint32_t)l * (uint32_t)d.in_s_b + (uint32_t)i * (uint32_t)d.in_s_line) *
+                             (uint32_t)sizeof(E);
+        v.set(q * U + u, *reinterpret_cast<const E*>(base + off));
       }
     }
   }
@@ -1313,7 +1233,7 @@ __device__ __forceinline__ void load_tile_any(const PassDesc& d, const void* in,
   constexpr int UG = green_stage<T, MC, K_ANY>();
   RegStage<T, E, U * NCL> v;
   GreenStage<T, UG> gs;
-  fetch<U, NCL, (MC <= 1), E>(v, d, in, ti);
+  fetch<U, NCL, E>(v, d, in, ti);
   if (d.fused) fetch_green<T, UG>(gs, d, ti);
   commit<U, NCL, E>(v, d, ti, smem);
   if (d.fused) commit_green<T, UG>(gs, d, ti, smem);
@@ -1372,7 +1292,7 @@ __device__ __forceinline__ void run_pipelined(const PassDesc& d, const void* in,
   RegStage<T, E, U * NCL> v;
   GreenStage<T, UG> gs;
   TileIdx ti = tile_index(d, tile);
-  fetch<U, NCL, false, E>(v, d, in, ti);
+  fetch<U, NCL, E>(v, d, in, ti);
   if constexpr (FUSED) fetch_green<T, UG>(gs, d, ti);
   // twiddle tables -> LDS (visible to the transform after the loop's barriers)
   cpx<T>* lt = reinterpret_cast<cpx<T>*>(smem + d.tab_off);
@@ -1397,7 +1317,7 @@ __device__ __forceinline__ void run_pipelined(const PassDesc& d, const void* in,
     TileIdx tn = ti;
     if (next >= 0) {
       tn = tile_index(d, next);
-      fetch<U, NCL, false, E>(v, d, in, tn);
+      fetch<U, NCL, E>(v, d, in, tn);
       if constexpr (FUSED) fetch_green<T, UG>(gs, d, tn);
     }
     compute<T, MC, KIND>(d, out, ti, smem, tb);
@@ -1438,7 +1358,7 @@ __device__ __forceinline__ void run_single(const PassDesc& d, const void* in, vo
     }
     RegStage<T, E, U * NCL> v;
     GreenStage<T, UG> gs;
-    fetch<U, NCL, (MC <= 1), E>(v, d, in, ti);
+    fetch<U, NCL, E>(v, d, in, ti);
     if constexpr (fused_of(KIND)) fetch_green<T, UG>(gs, d, ti);
     commit<U, NCL, E>(v, d, ti, smem);
     if constexpr (fused_of(KIND)) commit_green<T, UG>(gs, d, ti, smem);
@@ -1467,24 +1387,5 @@ void pass_kernel(const PassDesc* __restrict__ dp,
   if constexpr (PIPE && pipelined_kernel((int)sizeof(T), MC)) run_pipelined<T, MC, KIND>(*dp, in, out, smem);
   else run_single<T, MC, KIND>(*dp, in, out, smem);
 }
-
-// Batched form: tiles of many descriptors of one length class in one launch;
-// prefix[i] = first tile of descriptor i, prefix[n] = total.
-template <typename T, int MC>
-__global__ __launch_bounds__(kThreads) void pass_kernel_batched(const PassDesc* __restrict__ ds,
-                                                                const int* __restrict__ prefix,
-                                                                int n) {
-  extern __shared__ __align__(16) char smem[];
-  const int tile = blockIdx.x;
-  int lo = 0, hi = n - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (prefix[mid] <= tile) lo = mid;
-    else hi = mid - 1;
-  }
-  const PassDesc& d = ds[lo];
-  run_tile<T, MC>(d, d.in, d.out, tile - prefix[lo], smem);
-}
-
 
 }  // namespace fm

@@ -58,12 +58,23 @@ __global__ void wave_twiddle_kernel(cpx<T>* out, int M, int E) {
 }
 
 template <typename T>
-__global__ void twiddle_kernel(cpx<T>* out, int M) {
+__global__ void twiddle_kernel(cpx<T>* tw, int M, RtStages sch) {
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= 4 * M) return;
-  double s, c;
-  sincospi((double)j / (2.0 * (double)M), &s, &c);  // angle 2 pi j / (4 M)
-  out[j] = {T(c), T(-s)};
+  if (j >= 5 * M) return;
+  long long num = j, den = 4LL * M;  // angle 2 pi num / den
+  if (j >= 4 * M) {
+    int e = j - 4 * M, ns = 1, s = 0;
+    while (s < kRtStages && sch.r[s] > 1 && e >= ns * (sch.r[s] - 1)) {
+      e -= ns * (sch.r[s] - 1);
+      ns *= sch.r[s++];
+    }
+    if (s == kRtStages || sch.r[s] <= 1) return;  // past the last stage
+    den = (long long)ns * sch.r[s];
+    num = ((long long)(e % ns) * (e / ns + 1)) % den;
+  }
+  double sn, cs;
+  sincospi(2.0 * (double)num / (double)den, &sn, &cs);
+  tw[j] = {T(cs), T(-sn)};
 }
 
 // Regularised kernels (FM_GREEN_HEJ*): variant 2..6 is the order m = 2 (variant - 1),
@@ -264,15 +275,11 @@ template <typename T>
 hipError_t launch_pass(const PassDesc& d, const PassDesc* dev, const void* in, void* out,
                        hipStream_t st) {
   if (d.tiles <= 0) return hipSuccess;
-  if (d.stw == nullptr) {
-    if constexpr (sizeof(T) == 8)
-      if (d.M > kMaxFastLen64 || d.long_rt) return launch_len<T, kRtLong>(d, dev, in, out, st);
-    return launch_len<T, kRtShort>(d, dev, in, out, st);
-  }
+  if (d.stw == nullptr) return launch_len<T, kRuntime>(d, dev, in, out, st);
 #define FM_CALL(TT, M) launch_len<TT, M>(d, dev, in, out, st)
   switch (d.M) {
     FM_LEN_CASES(T, FM_CALL)
-    default: return launch_len<T, kRtShort>(d, dev, in, out, st);
+    default: return launch_len<T, kRuntime>(d, dev, in, out, st);
   }
 #undef FM_CALL
 }
@@ -285,19 +292,18 @@ hipError_t launch_pass_batched(int len_class, const PassDesc* ds, const int* pre
 #define FM_CALL(TT, M) launch_len_batched<TT, M>(ds, prefix, n, total_tiles, lds_bytes, st)
   switch (len_class) {
     FM_LEN_CASES(T, FM_CALL)
-    case kRtLong:
-      if constexpr (sizeof(T) == 8) return launch_len_batched<T, kRtLong>(ds, prefix, n, total_tiles, lds_bytes, st);
-      return hipErrorInvalidValue;
-    default: return launch_len_batched<T, kRtShort>(ds, prefix, n, total_tiles, lds_bytes, st);
+    default: return launch_len_batched<T, kRuntime>(ds, prefix, n, total_tiles, lds_bytes, st);
   }
 #undef FM_CALL
 }
 
 template <typename T>
-hipError_t launch_twiddles(void* out, int M, hipStream_t st) {
-  const int n = 4 * M;
+hipError_t launch_twiddles(void* out, int M, const int* rt_radix, int rt_n, hipStream_t st) {
+  RtStages sch{};
+  for (int s = 0; s < rt_n; ++s) sch.r[s] = rt_radix[s];
+  const int n = 5 * M;
   hipLaunchKernelGGL(twiddle_kernel<T>, dim3((n + 255) / 256), dim3(256), 0, st,
-                     reinterpret_cast<cpx<T>*>(out), M);
+                     reinterpret_cast<cpx<T>*>(out), M, sch);
   return hipGetLastError();
 }
 
@@ -388,8 +394,8 @@ template hipError_t launch_pass<float>(const PassDesc&, const PassDesc*, const v
 template hipError_t launch_pass<double>(const PassDesc&, const PassDesc*, const void*, void*, hipStream_t);
 template hipError_t launch_pass_batched<float>(int, const PassDesc*, const int*, int, int, int, hipStream_t);
 template hipError_t launch_pass_batched<double>(int, const PassDesc*, const int*, int, int, int, hipStream_t);
-template hipError_t launch_twiddles<float>(void*, int, hipStream_t);
-template hipError_t launch_twiddles<double>(void*, int, hipStream_t);
+template hipError_t launch_twiddles<float>(void*, int, const int*, int, hipStream_t);
+template hipError_t launch_twiddles<double>(void*, int, const int*, int, hipStream_t);
 template hipError_t launch_wave_twiddles<float>(void*, int, int, hipStream_t);
 template hipError_t launch_wave_twiddles<double>(void*, int, int, hipStream_t);
 template hipError_t launch_stage_twiddles<float>(void*, int, hipStream_t);

@@ -1,10 +1,11 @@
 // One (precision, length class) instantiation of the pass kernels, compiled once per
-// pair with -DFM_T=<float|double> -DFM_MC=<length, or kRtShort / kRtLong for the
-// runtime-length kernels>.
+// pair with -DFM_T=<float|double> -DFM_MC=<length, or kRuntime for the runtime-length
+// kernel>.
 #include <cstdlib>
 
 #include "fm_device.h"
 #include "fm_launch.h"
+#include "fm_rt.h"
 #include "fm_wave.h"
 
 #ifndef FM_T
@@ -24,6 +25,20 @@ static hipError_t allow_full_lds() {
   return once;
 }
 
+#if FM_MC == 0
+// Any length: one workgroup per tile.
+template <int KIND>
+static hipError_t launch_kind(const PassDesc& d, const PassDesc* dev, const void* in, void* out,
+                              hipStream_t st) {
+  if (d.rt_n < 1 || d.rt_threads < 64 || d.rt_threads > kRtThreads) return hipErrorInvalidValue;
+  if (d.lds_bytes > kSoftLds) {
+    const hipError_t e = allow_full_lds<&rt_kernel<FM_T, KIND>>();
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL((rt_kernel<FM_T, KIND>), dim3(d.tiles), dim3(d.rt_threads), d.lds_bytes, st, dev, in, out);
+  return hipGetLastError();
+}
+#else
 // Fused complex passes in the per-wavefront kernel with E values per lane, one workgroup
 // per tile.  Scalar lines: d.B / wave_lines(M, E) wavefronts per workgroup; curl lines:
 // three wavefronts (one per component) that walk the tile's d.B lines.  32 values per
@@ -144,6 +159,8 @@ static hipError_t launch_kind(const PassDesc& d, const PassDesc* dev, const void
                      st, dev, in, out);
   return hipGetLastError();
 }
+
+#endif  // FM_MC == 0
 
 template <>
 hipError_t launch_len<FM_T, FM_MC>(const PassDesc& d, const PassDesc* dev, const void* in,

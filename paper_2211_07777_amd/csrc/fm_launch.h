@@ -1,6 +1,5 @@
 // Per-length pass launchers.  Each (precision, length class) pair is compiled in its
-// own object from fm_inst.hip; length classes kRtShort / kRtLong are the runtime-length
-// kernels (kRtLong only in FP64).
+// own object from fm_inst.hip; length class 0 (kRuntime) is the runtime-length kernel.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -41,7 +40,6 @@ hipError_t launch_len_batched(const PassDesc* ds, const int* prefix, int n, int 
   FM_DECLARE_LEN(T, 4096)
 FM_DECLARE_PREC(float)
 FM_DECLARE_PREC(double)
-FM_DECLARE_LEN(double, 1)  // kRtLong: FP64 lines longer than kMaxFastLen64
 #undef FM_DECLARE_PREC
 #undef FM_DECLARE_LEN
 

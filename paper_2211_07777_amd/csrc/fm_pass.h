@@ -8,17 +8,15 @@ namespace fm {
 
 constexpr int kThreads = 256;    // threads per workgroup of every pass kernel
 constexpr int kCurlThreads = 192;  // per-wavefront curl kernel: a wavefront per component
-// Kernel length classes: a compile-time FFT length (> 1), or one of the two
-// runtime-length kernels.  FP64 lines longer than kMaxFastLen64 take the long class.
-constexpr int kRtShort = 0;
-constexpr int kRtLong = 1;
+// Kernel length classes: a compile-time FFT length (> 1), or the runtime-length kernel.
+constexpr int kRuntime = 0;
 constexpr int kMaxFastLen64 = 2048;
 // Values per thread held across a radix stage for lines of length M (or kernel length
 // class M).  FP64 holds 8 (radices up to 8), so that a stage, its butterfly temporaries
 // and the persistent kernels' prefetch of the next tile stay in VGPRs; FP64 lines
 // longer than kMaxFastLen64 need 16 and run one tile per workgroup without prefetch.
 constexpr int elems_per_thread(int real_bytes, int M) {
-  return (real_bytes == 4 || M == kRtLong || M > kMaxFastLen64) ? 16 : 8;
+  return (real_bytes == 4 || M > kMaxFastLen64) ? 16 : 8;
 }
 constexpr int max_radix(int real_bytes) { return real_bytes == 8 ? 8 : 16; }
 // Green's-spectrum values per thread staged with a fused tile (its nl rows of F_line
@@ -77,10 +75,18 @@ enum PassKind : int32_t {
 };
 constexpr int kNumKinds = 10;
 
-// Real-to-real transform in the form  y_q = sum_p w_p x_p cs(pi (p+a)(q+b) / nh),
-// evaluated as a length-2nh DFT of a symmetric extension with pre- and post-twiddles.
+// Real-to-real transform in the form  y_q = sum_p w_p x_p cs(pi (p+a)(q+b) / nh).
+// half = 0: a length-2nh DFT of a symmetric extension with pre- and post-twiddles.
+// The types II and III need only nh points (two real lines still share a complex FFT):
+// half = 1 (DCT-II, DST-II): the DFT of the samples reordered as x_0, x_2, ..., x_3, x_1,
+// whose spectrum V gives y_q = 2 Re(e^{-i pi q / 2 nh} V_q); half = 2 (DCT-III, DST-III):
+// the same steps backwards, V_m = e^{i pi m / 2 nh} (x_m - i x_{nh-m}) (Makhoul's N-point
+// algorithm).  The sine types are the cosine types of the line with alternating signs on
+// the side of the samples and reversed order on the side of the frequencies.
+enum R2RForm : int32_t { R2R_EXTEND = 0, R2R_II = 1, R2R_III = 2 };
 struct R2R {
-  int32_t nh;        // half period (FFT length M = 2 nh)
+  int32_t nh;        // half period (FFT length M = 2 nh, or nh when half != 0)
+  int32_t half;      // R2RForm
   int32_t a2, b2;    // 2a, 2b (0 or 1)
   int32_t sin;       // 0: cosine transform, 1: sine transform
   int32_t plo, phi;  // input index range (inclusive)
@@ -126,6 +132,17 @@ struct Fixup {
   int32_t b_dup, b_zero_lo, b_zero_hi, b_last;
   int32_t c_dup, c_zero_lo, c_zero_hi, c_last;
 };
+
+// Division by d in the runtime-length kernels: n / d = (n * rt_magic(d)) >> 32 for
+// n * d < 2^32 (0 stands for d = 1).
+constexpr uint32_t rt_magic(int d) {
+  return d <= 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + (uint32_t)d - 1) / (uint32_t)d);
+}
+struct RtStages {
+  int32_t r[8];  // radices; 0 past the last
+};
+constexpr int kRtThreads = 512;  // largest workgroup of the runtime-length kernels
+constexpr int kRtStages = 8;
 
 // Radix schedule of an FFT length: radix-16 stages first (when rmax allows), then one
 // of 8 / 4 / 2, then 3, 5 and 7.  Shared by the host (table generation) and the device (compile-time
@@ -254,8 +271,9 @@ struct PassDesc {
   // with the tile's input and keep them in LDS at g_off.  The transform itself then
   // reads no global memory, so the prefetch of the next tile overlaps it.
   int32_t tab_off, stw_n, tw_n;
-  int32_t long_rt;          // FP64: run in the runtime-length class with 16 values per
-                            // thread (a tile that does not fit 8, e.g. a 3-component curl)
+  int32_t force_rt;         // run in the runtime-length kernel although the length has a
+                            // compile-time one (no tile of it fits the registers, e.g. three
+                            // FP64 components, or the tile spans 4 GiB)
   int32_t g_off;
   uint64_t mag_gline;       // division by g.F_line
   int32_t lds_tabs;         // compile-time-length kernels that allow it: 1 = twiddle tables
@@ -267,6 +285,13 @@ struct PassDesc {
                             // Plain passes: four wavefronts, B = 4 wave_lines(M, E) FFT
                             // lines (times 2 real lines per FFT for the packed kinds)
   int32_t wave_rs;          // plain passes: raw tile line stride, in input elements
+  // Runtime-length kernel (fm_rt.h): its radix schedule and the multipliers of its index
+  // divisions (rt_magic) by M / R and by the product of the earlier radices per stage, by
+  // M, by the padding M - n_data, and by spec_n; 0 stages: the in-place kernels.
+  int32_t rt_n, rt_threads;
+  int32_t rt_radix[kRtStages];
+  uint32_t rt_mr[kRtStages], rt_ns[kRtStages];
+  uint32_t rt_mM, rt_mz, rt_msp;
   const void* wtw;          // its stage twiddle tables: E = 16 (wave_tw_size(M, 16) entries)
   const void* wtw8;         // and E = 8
   const void* wtw32;        // and E = 32 (FP32 Poisson fused passes)

@@ -26,7 +26,8 @@ hipError_t launch_pass(const PassDesc& d, const PassDesc* dev, const void* in, v
 template <typename T>
 hipError_t launch_pass_batched(int len_class, const PassDesc* ds, const int* prefix, int n,
                                int total_tiles, int lds_bytes, hipStream_t st);
-template <typename T> hipError_t launch_twiddles(void* out, int M, hipStream_t st);
+template <typename T>
+hipError_t launch_twiddles(void* out, int M, const int* rt_radix, int rt_n, hipStream_t st);
 template <typename T> hipError_t launch_stage_twiddles(void* out, int M, hipStream_t st);
 template <typename T> hipError_t launch_wave_twiddles(void* out, int M, int E, hipStream_t st);
 bool is_fast_len(int M);
@@ -86,6 +87,7 @@ struct AxisPlan {
   bool first_dft = false;
   // real-to-real axes
   int fwd = 0, bwd = 0, first = 0, nin = 0;
+  bool half = false;      // types II and III in FFTs of nh points (else 2 nh)
   int nspec = 0;          // spectral extent along this axis after its forward pass
   double nlog = 1;        // normalisation length
   // Green table
@@ -182,6 +184,7 @@ fm::R2R make_r2r(const AxisPlan& a, int kind, bool forward, bool common = false)
   const int n = a.nin;
   fm::R2R r{};
   r.nh = n + f.nh_add;
+  r.half = !a.half ? fm::R2R_EXTEND : (f.a2 ? fm::R2R_II : fm::R2R_III);
   r.a2 = f.a2;
   r.b2 = f.b2;
   r.sin = f.sin;
@@ -224,6 +227,44 @@ int radix_plan(int M, fm::PassDesc* d) {
   return FM_OK;
 }
 
+// Radix schedule of the runtime-length kernel: the cheapest product of its radices, by the
+// arithmetic of a point in each butterfly plus a stage's LDS round trip, address
+// arithmetic and barrier (a stage costs about as much as a radix-8 butterfly's
+// arithmetic and more, so few large radices win); the largest radix first, whose stage
+// needs no twiddles.
+struct RtRadix {
+  int r;
+  double cost;
+};
+constexpr RtRadix kRtRadix[] = {{16, 11}, {15, 16}, {12, 11}, {10, 13}, {9, 13}, {8, 7.5}, {7, 14},
+                                {6, 9},   {5, 10},  {4, 4},   {3, 6},   {2, 2}};
+constexpr double kRtStage = 14;
+
+double rt_search(int m, int from, int depth, int* cur, int* best, int* best_n, double cost, double best_cost) {
+  if (m == 1) {
+    if (cost < best_cost) {
+      best_cost = cost;
+      *best_n = depth;
+      std::copy(cur, cur + depth, best);
+    }
+    return best_cost;
+  }
+  if (depth == fm::kRtStages) return best_cost;
+  for (int i = from; i < (int)(sizeof(kRtRadix) / sizeof(kRtRadix[0])); ++i) {
+    const RtRadix& x = kRtRadix[i];
+    if (m % x.r || cost + x.cost + kRtStage >= best_cost) continue;
+    cur[depth] = x.r;
+    best_cost = rt_search(m / x.r, i, depth + 1, cur, best, best_n, cost + x.cost + kRtStage, best_cost);
+  }
+  return best_cost;
+}
+
+int rt_schedule(int M, int radix[fm::kRtStages]) {
+  int cur[fm::kRtStages], n = 0;
+  rt_search(M, 0, 0, cur, radix, &n, 0.0, 1e30);
+  return n;
+}
+
 // strides (elements) of a layout given its axis order (slow -> fast) and extents
 void layout_strides(const int order[3], const int ext[3], int64_t stride[3], int64_t* size) {
   int64_t s = 1;
@@ -255,7 +296,7 @@ struct fm_plan_s {
   // backward (spectrum -> B) transforms of fm_fft_forward / fm_fft_backward
   static constexpr int kPasses = 7;
   fm::PassDesc pass[kPasses];
-  bool long_rt[kPasses] = {};  // the pass needs the runtime-length class in the LDS-tile kernel
+  bool force_rt[kPasses] = {};  // the pass needs the runtime-length kernel in the LDS-tile modes
   const void* stw_plan[kPasses] = {};  // stage table of the planned kernel (null: runtime-length class)
   int ext_spec[3];
   int64_t Vspec;
@@ -397,15 +438,12 @@ constexpr bool kFp32OneLaunch = true;
 constexpr bool kFp32OneLaunch = false;
 #endif
 
-// Kernel length class that fixes the values per thread of a pass.
-int pass_class(const fm::PassDesc& d) { return d.long_rt ? fm::kRtLong : d.M; }
-
 // Whether a pass runs in the compile-time-length kernel of its FFT length (else in the
 // runtime-length kernel).  FP32 fused real-to-real passes of length 32 are kept on the
 // runtime-length kernel: the compile-time one ran only in a test that faulted the GPU,
 // and nothing has shown it free of that fault.
 bool compile_time_kernel(const fm::PassDesc& d, size_t elem) {
-  if (d.long_rt || !fm::is_fast_len(d.M)) return false;
+  if (d.force_rt || !fm::is_fast_len(d.M)) return false;
   if (!kFp32OneLaunch && elem == 4 && d.fused && d.gather == fm::G_R2R && d.M == 32) return false;
   return true;
 }
@@ -421,9 +459,92 @@ void set_lds_tables(fm::PassDesc* d, size_t elem) {
   if (d->gather == fm::G_R2R) d->tw_n = 2 * d->M;
 }
 
+// Runtime-length kernel: LDS of a tile of B lines (fm_rt.h): two buffers of the FFT lines,
+// the second also holding the raw lines of the kinds that gather.
+struct RtLds {
+  size_t raw_off, total;
+};
+RtLds rt_lds(const fm::PassDesc& d, int B, size_t elem, int comps) {
+  const int packs = (d.gather == fm::G_CPLX) ? 1 : 2;
+  const size_t cplx = 2 * elem;
+  const size_t F = (size_t)comps * ((B + packs - 1) / packs);
+  const size_t fft = F * fm::fft_line_stride(d.M) * cplx;
+  size_t second = fft;
+  if (d.gather == fm::G_HERM2) second = std::max(second, (size_t)B * (d.in_n | 1) * cplx);
+  if (d.gather == fm::G_R2R) {
+    second = std::max(second, F * (d.in_n | 1) * cplx);
+    if (d.fused) second = std::max(second, F * (d.spec_n | 1) * cplx);
+  }
+  const size_t off = round256(fft);
+  return {off, off + round256(second)};
+}
+
+// The largest FFT line (or three, for the curl) a tile may hold: what the register-held
+// tiles of earlier kernels took, and the limit stays.
+constexpr int kRtLongestTile = 4096;
+
+// A tile of B lines in the runtime-length kernel; false if it does not fit.
+bool set_rt(fm::PassDesc* d, size_t elem, int comps, int B) {
+  const int packs = (d->gather == fm::G_CPLX) ? 1 : 2;
+  if (comps * d->M > kRtLongestTile) return false;
+  const RtLds t = rt_lds(*d, B, elem, comps);
+  if (B < 1 || t.total > (size_t)fm::kMaxLds) return false;
+  int radix[fm::kRtStages];
+  const int n = rt_schedule(d->M, radix);
+  if (n < 1) return false;
+  d->rt_n = n;
+  int ns = 1;
+  for (int i = 0; i < n; ++i) {
+    d->rt_radix[i] = radix[i];
+    d->rt_mr[i] = fm::rt_magic(d->M / radix[i]);
+    d->rt_ns[i] = fm::rt_magic(ns);
+    ns *= radix[i];
+  }
+  d->rt_mM = fm::rt_magic(d->M);
+  d->rt_mz = fm::rt_magic(d->M - d->n_data);
+  d->rt_msp = fm::rt_magic(d->spec_n);
+  // about eight points per thread
+  const int points = comps * ((B + packs - 1) / packs) * d->M;
+  d->rt_threads = std::max(64, std::min(fm::kRtThreads, (points / 8 + 63) / 64 * 64));
+  d->B = B;
+  d->lds_bytes = (int)t.total;
+  d->raw_off = (int)t.raw_off;
+  d->g_off = d->tab_off = 0;
+  d->stw_n = d->tw_n = 0;
+  return true;
+}
+
+// The planner's tile of the runtime-length kernel: rows of at least 64 bytes on the side
+// that is strided, at least 1024 points, within the preferred LDS size (more for long
+// lines, down to half the rows); smaller while the pass has too few workgroups to fill
+// the chip.
+int choose_rt_tile(fm::PassDesc* d, size_t elem, int comps, int nb, int bmax, bool exact) {
+  const int packs = (d->gather == fm::G_CPLX) ? 1 : 2;
+  auto fits = [&](int B, size_t cap) { return rt_lds(*d, B, elem, comps).total <= cap; };
+  int B = std::max(1, std::min(bmax, nb));
+  if (!exact) {
+    int row = 1;
+    if (d->in_s_line != 1) row = std::max(row, (int)(64 / (elem * (d->in_cplx ? 2 : 1))));
+    if (d->out_s_line != 1) row = std::max(row, (int)(64 / (elem * (d->out_cplx ? 2 : 1))));
+    const int64_t groups = (int64_t)d->nc * std::max(1, d->ncomp);
+    int want = std::max(row, (1024 * packs + comps * d->M - 1) / (comps * d->M));
+    want = (want + packs - 1) / packs * packs;
+    B = std::min(B, want);
+    while (B > 2 * packs && ((nb + B - 1) / B) * groups < 512) B = (B / 2 + packs - 1) / packs * packs;
+    while (B > row && !fits(B, 40960)) --B;
+    while (B > (row + 1) / 2 && !fits(B, 81920)) --B;
+  }
+  while (B > 1 && !fits(B, fm::kMaxLds)) --B;
+  return set_rt(d, elem, comps, B) ? FM_OK : FM_E_SIZE;
+}
+
 // Largest tile (lines per workgroup) that fits the register budget and, if possible,
-// the preferred LDS size; otherwise the largest that fits the device's LDS.
-int choose_tile(fm::PassDesc* d, size_t elem, int comps, bool fused_r2r, int nb, int bmax = 64) {
+// the preferred LDS size; otherwise the largest that fits the device's LDS.  exact: of
+// the tuner and of callers that name a tile (runtime-length passes take the planner's
+// choice otherwise).
+int choose_tile(fm::PassDesc* d, size_t elem, int comps, bool fused_r2r, int nb, int bmax = 64, bool exact = false) {
+  d->rt_n = 0;
+  if (!compile_time_kernel(*d, elem)) return choose_rt_tile(d, elem, comps, nb, bmax, exact);
   const int packs = (d->gather == fm::G_CPLX) ? 1 : 2;
   set_lds_tables(d, elem);
   for (const int cap : {fm::kSoftLds, fm::kMaxLds}) {
@@ -431,7 +552,7 @@ int choose_tile(fm::PassDesc* d, size_t elem, int comps, bool fused_r2r, int nb,
     TileLds best_lds{};
     for (int B = 1; B <= bmax; ++B) {
       const int F = comps * ((B + packs - 1) / packs);
-      const int cls = pass_class(*d);
+      const int cls = d->M;
       if ((int64_t)F * d->M > (int64_t)fm::kThreads * fm::elems_per_thread((int)elem, cls)) break;
       // the register stage must hold the whole input tile (a Hermitian half-spectrum
       // pair has M + 2 values per FFT line), and a fused tile's Green rows
@@ -467,7 +588,7 @@ int wave_plain_rs(const fm::PassDesc& d, int E);
 
 bool wave_capable(const fm::PassDesc& d, size_t elem, int E) {
   // the kernels are compiled with the compile-time-length classes (fm_inst.hip)
-  if (d.long_rt || !fm::wave_length(d.M, E) || !fm::is_fast_len(d.M)) return false;
+  if (d.force_rt || !fm::wave_length(d.M, E) || !fm::is_fast_len(d.M)) return false;
   if (E == 32 && (!d.fused || d.g.curl || elem != 4)) return false;  // FP32 Poisson lines only
   if (!d.fused && d.gather == fm::G_R2R && d.out_cplx) return false;  // LDS-tile kernel only
   if (!d.fused) return wave_plain_rs(d, E) > 0;
@@ -503,7 +624,9 @@ size_t wave_plain_tab_bytes(const fm::PassDesc& d, int E, size_t elem) {
 }
 
 // Input values per thread of the plain per-wavefront kernel's register stage.
-int wave_plain_u(const fm::PassDesc& d, int E) { return d.gather == fm::G_REAL2 ? 2 * E + 1 : E + 1; }
+int wave_plain_u(const fm::PassDesc& d, int E) {
+  return d.gather == fm::G_REAL2 || d.gather == fm::G_R2R ? 2 * E + 1 : E + 1;
+}
 
 bool wave_capable(const fm::PassDesc& d, size_t elem) {
   return wave_capable(d, elem, 16) || wave_capable(d, elem, 8);
@@ -670,10 +793,12 @@ int make_tables_and_green(fm_plan_s* p, hipStream_t st, bool deferred) {
     const int M = p->pass[i].M;
     if (p->tw.count(M)) continue;
     void* ptr = nullptr;
-    if (plan_malloc(&ptr, sizeof(T) * 2 * 4 * (size_t)M) != hipSuccess) return FM_E_NOMEM;
+    if (plan_malloc(&ptr, sizeof(T) * 2 * 5 * (size_t)M) != hipSuccess) return FM_E_NOMEM;
     p->tw[M] = ptr;
-    p->table_bytes += sizeof(T) * 2 * 4 * (size_t)M;
-    FM_HIP(fm::launch_twiddles<T>(ptr, M, st));
+    p->table_bytes += sizeof(T) * 2 * 5 * (size_t)M;
+    int radix[fm::kRtStages];
+    const int nr = rt_schedule(M, radix);
+    FM_HIP(fm::launch_twiddles<T>(ptr, M, radix, nr, st));
   }
   for (int i = 0; i < fm_plan_s::kPasses; ++i) p->pass[i].tw = p->tw[p->pass[i].M];
   // per-stage tables of the lengths with compile-time kernels; also of a pass planned in
@@ -683,10 +808,9 @@ int make_tables_and_green(fm_plan_s* p, hipStream_t st, bool deferred) {
   for (int i = 0; i < fm_plan_s::kPasses; ++i) {
     const int M = p->pass[i].M;
     fm::PassDesc c = p->pass[i];
-    c.long_rt = 0;
+    c.force_rt = 0;
     const bool planned = compile_time_kernel(p->pass[i], p->elem);
-    if (!planned && !(p->long_rt[i] && wave_capable(c, p->elem))) continue;
-    if (tile_in_span_bytes(p->pass[i], p->elem) >= (int64_t(1) << 32)) continue;
+    if (!planned && !(p->force_rt[i] && wave_capable(c, p->elem))) continue;
     if (!p->stw.count(M)) {
       void* ptr = nullptr;
       const size_t n = (size_t)std::max(1, fm::stage_table_size(M, fm::max_radix((int)sizeof(T))));
@@ -697,13 +821,13 @@ int make_tables_and_green(fm_plan_s* p, hipStream_t st, bool deferred) {
     }
     if (planned) p->pass[i].stw = p->stw[M];
   }
-  for (int i = 0; i < fm_plan_s::kPasses; ++i) p->stw_plan[i] = p->long_rt[i] ? nullptr : p->pass[i].stw;
+  for (int i = 0; i < fm_plan_s::kPasses; ++i) p->stw_plan[i] = p->force_rt[i] ? nullptr : p->pass[i].stw;
 
   // stage twiddles of the per-wavefront kernels (a pass may run there, now or after
   // tuning), one table per length and values per lane
   for (int i = 0; i < 5; ++i) {
     fm::PassDesc w = p->pass[i];
-    w.long_rt = 0;  // the per-wavefront kernels take the compile-time length class
+    w.force_rt = 0;  // the per-wavefront kernels take the compile-time length class
     for (const int E : {16, 8, 32}) {
       if (!wave_capable(w, p->elem, E)) continue;
       const int M = p->pass[i].M;
@@ -881,6 +1005,7 @@ int make_tables_and_green(fm_plan_s* p, hipStream_t st, bool deferred) {
     d.nc = Fs[lc];
     d.ncomp = 1;
     d.in_n = d.out_n = n;
+    d.force_rt = 1;  // no stage tables are made for the generation
     if ((rc = choose_tile(&d, sizeof(double), 1, false, d.nb))) break;
     d.tiles = ((d.nb + d.B - 1) / d.B) * d.nc;
     set_magics(&d);
@@ -888,9 +1013,11 @@ int make_tables_and_green(fm_plan_s* p, hipStream_t st, bool deferred) {
     void* t64 = nullptr;
     auto it = p->tw64.find(d.M);
     if (it == p->tw64.end()) {
-      if (plan_malloc(&t64, sizeof(double) * 2 * 4 * (size_t)d.M) != hipSuccess) { rc = FM_E_NOMEM; break; }
+      if (plan_malloc(&t64, sizeof(double) * 2 * 5 * (size_t)d.M) != hipSuccess) { rc = FM_E_NOMEM; break; }
       p->tw64[d.M] = t64;
-      FM_HIP(fm::launch_twiddles<double>(t64, d.M, st));
+      int radix[fm::kRtStages];
+      const int nr = rt_schedule(d.M, radix);
+      FM_HIP(fm::launch_twiddles<double>(t64, d.M, radix, nr, st));
     } else {
       t64 = it->second;
     }
@@ -1038,7 +1165,10 @@ bool pass_in_bounds(const fm::PassDesc& d, int64_t in_size, int64_t out_size, si
   int prodR = 1;
   for (int i = 0; i < d.nstages; ++i) prodR *= d.radix[i];
   if (prodR != M || M < 2 || M > fm::kMaxLen) return false;
-  auto r2r_ok = [&](const fm::R2R& r) { return 2 * r.nh == M && r.qhi < M && r.qlo >= 0 && r.plo >= 0 && r.phi <= r.nh; };
+  auto r2r_ok = [&](const fm::R2R& r) {
+    return (r.half ? r.nh == M && r.qhi <= M && r.qhi - r.qlo < M : 2 * r.nh == M && r.qhi < M) && r.qlo >= 0 &&
+           r.plo >= 0 && r.phi <= r.nh;
+  };
   switch (d.gather) {
     case fm::G_CPLX: case fm::G_REAL2: if (d.n_data > d.in_n || d.n_data > M) return false; break;
     case fm::G_HERM2: if (d.in_n < M / 2 + 1) return false; break;
@@ -1083,8 +1213,22 @@ bool pass_in_bounds(const fm::PassDesc& d, int64_t in_size, int64_t out_size, si
     const int nbt = (d.nb + d.B - 1) / d.B;
     return d.tiles == nbt * d.nc * d.ncomp;
   }
-  const int cls = pass_class(d);
-  if (d.long_rt && elem != 8) return false;
+  if (d.rt_n) {
+    // runtime-length kernel: its schedule, and the two LDS buffers
+    int prod = 1;
+    for (int i = 0; i < d.rt_n; ++i) {
+      if (d.rt_mr[i] != fm::rt_magic(M / d.rt_radix[i]) || d.rt_ns[i] != fm::rt_magic(prod)) return false;
+      prod *= d.rt_radix[i];
+    }
+    const RtLds t = rt_lds(d, d.B, elem, comps);
+    if (prod != M || comps * M > kRtLongestTile || d.stw_n + d.tw_n != 0) return false;
+    if ((size_t)d.raw_off != t.raw_off || (size_t)d.lds_bytes < t.total || d.lds_bytes > fm::kMaxLds) return false;
+    if (d.rt_threads < 64 || d.rt_threads > fm::kRtThreads || d.rt_threads % 64) return false;
+    const int nbt = (d.nb + d.B - 1) / d.B;
+    return d.tiles == nbt * d.nc * (comps == 3 ? 1 : d.ncomp);
+  }
+  if (!compile_time_kernel(d, elem)) return false;
+  const int cls = M;
   if ((int64_t)F * M > (int64_t)fm::kThreads * fm::elems_per_thread((int)elem, cls)) return false;
   if ((int64_t)d.B * d.in_n > (int64_t)fm::kThreads * fm::stage_values((int)elem, cls, d.in_cplx != 0, comps))
     return false;
@@ -1178,6 +1322,21 @@ int build_plan(fm_plan_s* p) {
   int ord[3] = {0, 1, 2};
   std::stable_sort(ord, ord + 3, [&](int x, int y) { return cost(p->ax[x].cls) < cost(p->ax[y].cls); });
   for (int i = 0; i < 3; ++i) p->order[i] = ord[i];
+  for (int i = 0; i < 3; ++i) {
+    // real-to-real axes of the types II and III take FFTs of nh points instead of 2 nh in
+    // the runtime-length kernel; lengths 2 nh with a compile-time kernel keep it (they are
+    // bound by the tile's loads and stores: halving the transform of the 128-point lines
+    // of the mixed 128 x 128 x 256 workload changed no pass by more than 0.6 us of 18)
+    AxisPlan& a = p->ax[ord[i]];
+    if (a.dft || a.M > fm::kMaxLen || fm::is_fast_len(a.M)) continue;  // (longer ones stay refused)
+    const KindForm f = kind_form(a.fwd);
+    if (f.a2 == f.b2 || a.M < 4) continue;  // types I and IV
+    a.half = true;
+    a.M /= 2;
+  }
+  if (p->vec)
+    for (int q = 0; q < 3; ++q)
+      for (int a = 0; a < 3; ++a) vin[q][a].half = vout[q][a].half = p->ax[a].half;
   bool seen_dft = false;
   for (int i = 0; i < 3; ++i) {
     AxisPlan& a = p->ax[ord[i]];
@@ -1470,21 +1629,24 @@ int build_plan(fm_plan_s* p) {
     if (rc) return rc;
     const bool fused_curl = (i == 2) && curl && !p->vec3;
     d.ncomp = vec_pass(p, i) ? 1 : p->ncomp;  // launched per component
-    d.long_rt = 0;
+    d.force_rt = 0;
     d.persist = 1;
     d.lds_tabs = 1;
-    int rc2 = choose_tile(&d, p->elem, fused_curl ? 3 : 1, (i == 2) && d.gather == fm::G_R2R, d.nb);
-    if (rc2 && p->prec == FM_F64) {
-      // no tile fits 8 FP64 values per thread: the runtime-length class with 16
-      d.long_rt = 1;
-      p->long_rt[i] = true;
-      rc2 = choose_tile(&d, p->elem, fused_curl ? 3 : 1, (i == 2) && d.gather == fm::G_R2R, d.nb);
+    const int comps = fused_curl ? 3 : 1;
+    const bool fused_r2r = (i == 2) && d.gather == fm::G_R2R;
+    int rc2 = choose_tile(&d, p->elem, comps, fused_r2r, d.nb);
+    if (rc2 ? p->prec == FM_F64 : !d.rt_n && tile_in_span_bytes(d, p->elem) >= (int64_t(1) << 32)) {
+      // no tile fits the registers of a compile-time kernel (three FP64 components), or a
+      // tile spans more than its 32-bit offsets reach
+      d.force_rt = 1;
+      p->force_rt[i] = true;
+      rc2 = choose_tile(&d, p->elem, comps, fused_r2r, d.nb);
     }
     if (rc2) return rc2;
     d.tiles = ((d.nb + d.B - 1) / d.B) * d.nc * (fused_curl ? 1 : d.ncomp);
     set_magics(&d);
     fm::PassDesc wd = d;  // the per-wavefront kernels have the compile-time length class
-    wd.long_rt = 0;
+    wd.force_rt = 0;
     const int64_t lines = (int64_t)d.nb * d.nc;
     if (i == 2 && wave_capable(wd, p->elem) && !(fused_curl && p->elem == 8 && lines < kCurlWaveLines64)) {
       // the per-wavefront kernel, with the most wavefronts per workgroup whose LDS stays
@@ -1690,8 +1852,7 @@ int build_batch(int count, const fm_plan* plans, const void* const* rhs_dev, voi
         by_class[-1 - i].push_back(i);
         continue;
       }
-      const int rt = (d.M > fm::kMaxFastLen64 || d.long_rt) ? fm::kRtLong : fm::kRtShort;
-      by_class[d.stw ? d.M : rt].push_back(i);
+      by_class[d.rt_n ? fm::kRuntime : d.M].push_back(i);
     }
     for (auto& kv : by_class) {
       fm_batch_s::Group g{};
@@ -1960,7 +2121,7 @@ int fm_plan_inspect(const int n[3], const double h[3], const int bc[3][2], int l
     for (int a = 0; a < 3; ++a) {
       info->order[a] = p->order[a];
       info->axis_class[a] = p->ax[a].cls;
-      info->fft_len[a] = p->ax[a].M;
+      info->fft_len[a] = p->ax[a].M * (p->ax[a].half ? 2 : 1);
       info->spec_len[a] = p->ax[a].nspec;
       info->green_dims[a] = p->ax[p->order[a]].F;
     }
@@ -2138,7 +2299,7 @@ bool retile(const fm_plan_s* p, int i, int bmax, int mode, fm::PassDesc* out) {
   // the per-wavefront kernel has the compile-time length; the LDS-tile kernel takes the
   // class the plan chose
   const bool wave_mode = mode >= 3;
-  d.long_rt = wave_mode ? 0 : p->long_rt[i];
+  d.force_rt = wave_mode ? 0 : p->force_rt[i];
   d.stw = p->stw_plan[i];
   if (wave_mode) {
     // the per-wavefront kernel (16 or 8 values per lane): the most wavefronts per
@@ -2163,7 +2324,7 @@ bool retile(const fm_plan_s* p, int i, int bmax, int mode, fm::PassDesc* out) {
   }
   d.persist = mode == 1;
   d.lds_tabs = mode != 2;
-  if (choose_tile(&d, p->elem, fused_curl ? 3 : 1, (i == 2) && d.gather == fm::G_R2R, d.nb, bmax))
+  if (choose_tile(&d, p->elem, fused_curl ? 3 : 1, (i == 2) && d.gather == fm::G_R2R, d.nb, bmax, true))
     return false;
   d.tiles = ((d.nb + d.B - 1) / d.B) * d.nc * (fused_curl ? 1 : d.ncomp);
   set_magics(&d);

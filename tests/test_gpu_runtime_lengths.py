@@ -1,0 +1,75 @@
+"""The runtime-length kernel (lengths without a compile-time kernel) against the FP64
+oracle: every radix and schedule depth, odd and even line counts, lines shorter than a
+wavefront and the longest ones, all three forms of the real-to-real transforms, tiles of
+one line and of several.  Tolerances are those of every parity test (FP64 1e-12, FP32 1e-5
+relative L-infinity)."""
+import numpy as np
+import pytest
+
+import oracle as O
+import paper_2211_07777_amd as F
+from gpu_common import TOL32, TOL64, check_conventions, gpu_solve, oracle_solve, rel_linf
+
+pytestmark = pytest.mark.gpu
+U, P, E, D = 3, 2, 0, 1
+FACES = [[P, P], [U, U], [E, E], [D, D], [E, D], [D, E], [E, U], [D, U], [U, E], [U, D]]
+# 2 3 5 7 9 (3.3), 15, 25, 27, 35, 45, 49, 63, 75, 81, 105, 125, 210, 243, 343
+LENGTHS = [2, 3, 5, 7, 9, 15, 25, 27, 35, 45, 49, 63, 75, 81, 105, 125, 210, 243, 343]
+
+
+@pytest.mark.parametrize("prec,tol", [(F.F64, TOL64), (F.F32, TOL32)])
+@pytest.mark.parametrize("layout", [F.CELL, F.NODE])
+@pytest.mark.parametrize("axis", [0, 1, 2])
+def test_lengths_and_forms(axis, layout, prec, tol):
+    rng = np.random.default_rng(7 * axis + 3 * layout + prec)
+    for i, N in enumerate(LENGTHS):
+        faces = FACES[(3 * i + axis) % len(FACES)]
+        n, bc = [5, 6, 4], [list(FACES[rng.integers(len(FACES))]) for _ in range(3)]
+        n[axis], bc[axis] = N, list(faces)
+        h = [0.11, 0.09, 0.1]
+        f = rng.standard_normal(O.user_shape(n, layout))
+        ref = oracle_solve(f, n, h, bc, layout)
+        plan = F.Plan(n, h, bc, layout, F.CHAT2, prec)
+        t = plan.tiling()
+        for lines in (None, 1, 3):
+            if lines is not None:
+                b = [lines if q == 2 else v for v, q in zip(t["lines_per_tile"], t["persistent"])]
+                try:
+                    plan.set_tiling(b, t["persistent"])
+                except F.FluxmiError:  # a pass with fewer lines than that
+                    continue
+            u = gpu_solve(plan, f)
+            check_conventions(u, bc, layout)
+            err = rel_linf(u, ref)
+            assert err < tol, (n, bc, layout, prec, lines, err)
+        plan.close()
+
+
+@pytest.mark.parametrize("prec,tol", [(F.F64, TOL64), (F.F32, TOL32)])
+@pytest.mark.parametrize("n,bc", [([2000, 3, 4], [[U, U], [P, P], [E, E]]),   # a 4000-point DFT
+                                  ([3, 1000, 4], [[P, P], [D, U], [U, U]]),   # 4000-point extension
+                                  ([3, 4, 1800], [[E, D], [P, P], [U, U]]),   # fused, 3600 points
+                                  ([4, 3, 1875], [[E, E], [D, D], [E, D]])])  # fused real-to-real
+def test_longest_lines(n, bc, prec, tol):
+    for layout in (F.CELL, F.NODE):
+        h = [2.0 / max(n)] * 3
+        f = np.random.default_rng(11).standard_normal(O.user_shape(n, layout))
+        plan = F.Plan(n, h, bc, layout, F.CHAT2, prec)
+        err = rel_linf(gpu_solve(plan, f), oracle_solve(f, n, h, bc, layout))
+        plan.close()
+        assert err < tol, (n, layout, err)
+
+
+@pytest.mark.parametrize("prec,tol", [(F.F64, TOL64), (F.F32, TOL32)])
+def test_curl_lines_and_refusal(prec, tol):
+    """Three components: the longest lines taken (3 x 1350 points in a tile), and the first
+    refused length (3 x 1400)."""
+    n, h, bc = [4, 3, 675], [0.1, 0.1, 2 / 675], [[U, U], [P, P], [U, U]]
+    f = np.random.default_rng(5).standard_normal((3,) + O.user_shape(n, O.CELL))
+    plan = F.Plan(n, h, bc, F.CELL, F.CHAT2, prec, F.BIOT_SAVART, 3)
+    err = rel_linf(gpu_solve(plan, f), oracle_solve(f, n, h, bc, O.CELL, 0, 1))
+    plan.close()
+    assert err < tol, err
+    with pytest.raises(F.FluxmiError) as e:
+        F.plan_inspect([4, 3, 700], h, bc, F.CELL, F.CHAT2, prec, F.BIOT_SAVART, 3)
+    assert e.value.status == -3
