@@ -1255,7 +1255,11 @@ __device__ __forceinline__ void run_tile(const PassDesc& d, const void* in, void
 // contiguous ranges, one per XCD, and the blocks of an XCD walk their range side by side:
 // tiles that are neighbours along the tile axis (and share cache lines of a strided
 // input or output) run at the same time on the same L2.  Tile k of block b (k = 0, 1,
-// ...) is returned, or -1 past the end of the block's share.
+// ...) is returned, or -1 past the end of the block's share.  The ranges differ by at
+// most one tile, longer ones first, as the numbers of blocks do: a grid of one block per
+// tile gives every block exactly one.  (With ranges of equal length, rounded up, some
+// blocks took two tiles one after the other whenever the count was no multiple of 8: a
+// real-to-real pass of 33^3 points ran 13.4 us against 8.0 of 32^3.)
 constexpr int kXcds = 8;
 __device__ __forceinline__ int xcd_tile(int b, int grid, int k, int tiles) {
   if (grid < kXcds) {  // too few blocks to give every XCD a share: plain striding
@@ -1263,12 +1267,12 @@ __device__ __forceinline__ int xcd_tile(int b, int grid, int k, int tiles) {
     return t < tiles ? t : -1;
   }
   const int x = b % kXcds, j = b / kXcds;
-  const int per = (tiles + kXcds - 1) / kXcds;       // tiles of one XCD
-  const int nbx = (grid - x + kXcds - 1) / kXcds;    // blocks on XCD x
+  const int rem = tiles % kXcds;
+  const int per = tiles / kXcds + (x < rem ? 1 : 0);  // tiles of this XCD
+  const int nbx = (grid - x + kXcds - 1) / kXcds;     // blocks on XCD x
   const int local = j + k * nbx;
   if (local >= per) return -1;
-  const int t = x * per + local;
-  return t < tiles ? t : -1;
+  return x * (tiles / kXcds) + min(x, rem) + local;
 }
 
 // Persistent loop over the tiles of a pass: while tile t is transformed in LDS, the
