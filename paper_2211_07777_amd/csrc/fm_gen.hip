@@ -298,9 +298,11 @@ hipError_t launch_pass_batched(int len_class, const PassDesc* ds, const int* pre
 }
 
 template <typename T>
-hipError_t launch_twiddles(void* out, int M, const int* rt_radix, int rt_n, hipStream_t st) {
+hipError_t launch_twiddles(void* out, int M, hipStream_t st) {
   RtStages sch{};
-  for (int s = 0; s < rt_n; ++s) sch.r[s] = rt_radix[s];
+  int radix[kRtStages];
+  const int stages = rt_schedule(M, radix);
+  for (int s = 0; s < stages; ++s) sch.r[s] = radix[s];
   const int n = 5 * M;
   hipLaunchKernelGGL(twiddle_kernel<T>, dim3((n + 255) / 256), dim3(256), 0, st,
                      reinterpret_cast<cpx<T>*>(out), M, sch);
@@ -394,8 +396,8 @@ template hipError_t launch_pass<float>(const PassDesc&, const PassDesc*, const v
 template hipError_t launch_pass<double>(const PassDesc&, const PassDesc*, const void*, void*, hipStream_t);
 template hipError_t launch_pass_batched<float>(int, const PassDesc*, const int*, int, int, int, hipStream_t);
 template hipError_t launch_pass_batched<double>(int, const PassDesc*, const int*, int, int, int, hipStream_t);
-template hipError_t launch_twiddles<float>(void*, int, const int*, int, hipStream_t);
-template hipError_t launch_twiddles<double>(void*, int, const int*, int, hipStream_t);
+template hipError_t launch_twiddles<float>(void*, int, hipStream_t);
+template hipError_t launch_twiddles<double>(void*, int, hipStream_t);
 template hipError_t launch_wave_twiddles<float>(void*, int, int, hipStream_t);
 template hipError_t launch_wave_twiddles<double>(void*, int, int, hipStream_t);
 template hipError_t launch_stage_twiddles<float>(void*, int, hipStream_t);

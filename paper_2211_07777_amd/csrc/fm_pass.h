@@ -138,11 +138,49 @@ struct Fixup {
 constexpr uint32_t rt_magic(int d) {
   return d <= 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + (uint32_t)d - 1) / (uint32_t)d);
 }
-struct RtStages {
-  int32_t r[8];  // radices; 0 past the last
-};
 constexpr int kRtThreads = 512;  // largest workgroup of the runtime-length kernels
 constexpr int kRtStages = 8;
+struct RtStages {
+  int32_t r[kRtStages];  // radices; 0 past the last
+};
+
+// Radix schedule of the runtime-length kernel: the cheapest product of its radices, by the
+// arithmetic of a point in each butterfly plus a stage's LDS round trip, address
+// arithmetic and barrier (a stage costs more than a radix-8 butterfly's arithmetic, so few
+// large radices win); the largest radix first, whose stage needs no twiddles.
+struct RtRadix {
+  int r;
+  double cost;
+};
+constexpr RtRadix kRtRadix[] = {{16, 11}, {15, 16}, {12, 11}, {10, 13}, {9, 13}, {8, 7.5}, {7, 14},
+                                {6, 9},   {5, 10},  {4, 4},   {3, 6},   {2, 2}};
+constexpr int kRtRadices = sizeof(kRtRadix) / sizeof(kRtRadix[0]);
+constexpr double kRtStage = 14;
+
+inline double rt_search(int m, int from, int depth, int* cur, int* best, int* best_n, double cost,
+                        double best_cost) {
+  if (m == 1) {
+    if (cost >= best_cost) return best_cost;
+    *best_n = depth;
+    for (int i = 0; i < depth; ++i) best[i] = cur[i];
+    return cost;
+  }
+  if (depth == kRtStages) return best_cost;
+  for (int i = from; i < kRtRadices; ++i) {
+    const double c = cost + kRtRadix[i].cost + kRtStage;
+    if (m % kRtRadix[i].r || c >= best_cost) continue;
+    cur[depth] = kRtRadix[i].r;
+    best_cost = rt_search(m / kRtRadix[i].r, i, depth + 1, cur, best, best_n, c, best_cost);
+  }
+  return best_cost;
+}
+
+// The radices of length M in radix[]; returns their number (0: no such product).
+inline int rt_schedule(int M, int radix[kRtStages]) {
+  int cur[kRtStages], n = 0;
+  rt_search(M, 0, 0, cur, radix, &n, 0.0, 1e30);
+  return n;
+}
 
 // Radix schedule of an FFT length: radix-16 stages first (when rmax allows), then one
 // of 8 / 4 / 2, then 3, 5 and 7.  Shared by the host (table generation) and the device (compile-time
@@ -274,6 +312,7 @@ struct PassDesc {
   int32_t force_rt;         // run in the runtime-length kernel although the length has a
                             // compile-time one (no tile of it fits the registers, e.g. three
                             // FP64 components, or the tile spans 4 GiB)
+  int32_t mode_rt;          // launch mode 6: the runtime-length kernel by choice
   int32_t g_off;
   uint64_t mag_gline;       // division by g.F_line
   int32_t lds_tabs;         // compile-time-length kernels that allow it: 1 = twiddle tables

@@ -26,8 +26,7 @@ hipError_t launch_pass(const PassDesc& d, const PassDesc* dev, const void* in, v
 template <typename T>
 hipError_t launch_pass_batched(int len_class, const PassDesc* ds, const int* prefix, int n,
                                int total_tiles, int lds_bytes, hipStream_t st);
-template <typename T>
-hipError_t launch_twiddles(void* out, int M, const int* rt_radix, int rt_n, hipStream_t st);
+template <typename T> hipError_t launch_twiddles(void* out, int M, hipStream_t st);
 template <typename T> hipError_t launch_stage_twiddles(void* out, int M, hipStream_t st);
 template <typename T> hipError_t launch_wave_twiddles(void* out, int M, int E, hipStream_t st);
 bool is_fast_len(int M);
@@ -227,44 +226,6 @@ int radix_plan(int M, fm::PassDesc* d) {
   return FM_OK;
 }
 
-// Radix schedule of the runtime-length kernel: the cheapest product of its radices, by the
-// arithmetic of a point in each butterfly plus a stage's LDS round trip, address
-// arithmetic and barrier (a stage costs about as much as a radix-8 butterfly's
-// arithmetic and more, so few large radices win); the largest radix first, whose stage
-// needs no twiddles.
-struct RtRadix {
-  int r;
-  double cost;
-};
-constexpr RtRadix kRtRadix[] = {{16, 11}, {15, 16}, {12, 11}, {10, 13}, {9, 13}, {8, 7.5}, {7, 14},
-                                {6, 9},   {5, 10},  {4, 4},   {3, 6},   {2, 2}};
-constexpr double kRtStage = 14;
-
-double rt_search(int m, int from, int depth, int* cur, int* best, int* best_n, double cost, double best_cost) {
-  if (m == 1) {
-    if (cost < best_cost) {
-      best_cost = cost;
-      *best_n = depth;
-      std::copy(cur, cur + depth, best);
-    }
-    return best_cost;
-  }
-  if (depth == fm::kRtStages) return best_cost;
-  for (int i = from; i < (int)(sizeof(kRtRadix) / sizeof(kRtRadix[0])); ++i) {
-    const RtRadix& x = kRtRadix[i];
-    if (m % x.r || cost + x.cost + kRtStage >= best_cost) continue;
-    cur[depth] = x.r;
-    best_cost = rt_search(m / x.r, i, depth + 1, cur, best, best_n, cost + x.cost + kRtStage, best_cost);
-  }
-  return best_cost;
-}
-
-int rt_schedule(int M, int radix[fm::kRtStages]) {
-  int cur[fm::kRtStages], n = 0;
-  rt_search(M, 0, 0, cur, radix, &n, 0.0, 1e30);
-  return n;
-}
-
 // strides (elements) of a layout given its axis order (slow -> fast) and extents
 void layout_strides(const int order[3], const int ext[3], int64_t stride[3], int64_t* size) {
   int64_t s = 1;
@@ -297,6 +258,7 @@ struct fm_plan_s {
   static constexpr int kPasses = 7;
   fm::PassDesc pass[kPasses];
   bool force_rt[kPasses] = {};  // the pass needs the runtime-length kernel in the LDS-tile modes
+  int line_M[kPasses] = {};  // FFT length of the pass outside launch mode 6
   const void* stw_plan[kPasses] = {};  // stage table of the planned kernel (null: runtime-length class)
   int ext_spec[3];
   int64_t Vspec;
@@ -438,12 +400,19 @@ constexpr bool kFp32OneLaunch = true;
 constexpr bool kFp32OneLaunch = false;
 #endif
 
+// The real-to-real form of a plain pass of extension length M (types II and III) in the
+// runtime-length kernel; R2R_EXTEND for the other types and passes.
+int runtime_form(const fm::PassDesc& d) {
+  if (d.fused || d.gather != fm::G_R2R || d.r2r.a2 == d.r2r.b2) return fm::R2R_EXTEND;
+  return d.r2r.a2 ? fm::R2R_II : fm::R2R_III;
+}
+
 // Whether a pass runs in the compile-time-length kernel of its FFT length (else in the
 // runtime-length kernel).  FP32 fused real-to-real passes of length 32 are kept on the
 // runtime-length kernel: the compile-time one ran only in a test that faulted the GPU,
 // and nothing has shown it free of that fault.
 bool compile_time_kernel(const fm::PassDesc& d, size_t elem) {
-  if (d.force_rt || !fm::is_fast_len(d.M)) return false;
+  if (d.force_rt || d.mode_rt || !fm::is_fast_len(d.M)) return false;
   if (!kFp32OneLaunch && elem == 4 && d.fused && d.gather == fm::G_R2R && d.M == 32) return false;
   return true;
 }
@@ -482,6 +451,8 @@ RtLds rt_lds(const fm::PassDesc& d, int B, size_t elem, int comps) {
 // The largest FFT line (or three, for the curl) a tile may hold: what the register-held
 // tiles of earlier kernels took, and the limit stays.
 constexpr int kRtLongestTile = 4096;
+// Passes of fewer points than this wait on latencies more than on any throughput.
+constexpr int64_t kRtSmall = 1 << 18;
 
 // A tile of B lines in the runtime-length kernel; false if it does not fit.
 bool set_rt(fm::PassDesc* d, size_t elem, int comps, int B) {
@@ -490,7 +461,7 @@ bool set_rt(fm::PassDesc* d, size_t elem, int comps, int B) {
   const RtLds t = rt_lds(*d, B, elem, comps);
   if (B < 1 || t.total > (size_t)fm::kMaxLds) return false;
   int radix[fm::kRtStages];
-  const int n = rt_schedule(d->M, radix);
+  const int n = fm::rt_schedule(d->M, radix);
   if (n < 1) return false;
   d->rt_n = n;
   int ns = 1;
@@ -503,9 +474,16 @@ bool set_rt(fm::PassDesc* d, size_t elem, int comps, int B) {
   d->rt_mM = fm::rt_magic(d->M);
   d->rt_mz = fm::rt_magic(d->M - d->n_data);
   d->rt_msp = fm::rt_magic(d->spec_n);
-  // about eight points per thread
+  // Points per thread: eight in FP32 and in the fused kinds, five in the plain kinds of
+  // FP64, whose butterflies hold twice the registers, so that more wavefronts are needed to
+  // cover the same latency.  Whole solves with five / eight / twelve points: 320 x 250 x 180
+  // FP32 1425 / 1337 / 1326 us, 240 x 200 x 160 FP32 457 / 455 / 497; 200 x 150 x 120 FP64
+  // 239 / 254 / 292, 200^3 FP64 262 / 274 / 322 (a fused pass of 360 points 1132 / 1043).
+  // Small passes wait on latencies and take two.
   const int points = comps * ((B + packs - 1) / packs) * d->M;
-  d->rt_threads = std::max(64, std::min(fm::kRtThreads, (points / 8 + 63) / 64 * 64));
+  const int64_t all = (int64_t)points * ((d->nb + B - 1) / B) * d->nc * std::max(1, d->ncomp);
+  const int per = all < kRtSmall ? 2 : elem == 8 && !d->fused ? 5 : 8;
+  d->rt_threads = std::max(64, std::min(fm::kRtThreads, (points / per + 63) / 64 * 64));
   d->B = B;
   d->lds_bytes = (int)t.total;
   d->raw_off = (int)t.raw_off;
@@ -515,9 +493,9 @@ bool set_rt(fm::PassDesc* d, size_t elem, int comps, int B) {
 }
 
 // The planner's tile of the runtime-length kernel: rows of at least 64 bytes on the side
-// that is strided, at least 1024 points, within the preferred LDS size (more for long
-// lines, down to half the rows); smaller while the pass has too few workgroups to fill
-// the chip.
+// that is strided, at least 1024 points, within an LDS size that leaves room for several
+// workgroups on a CU (more for long lines, down to half the rows); smaller while the pass
+// has too few workgroups to fill the chip.
 int choose_rt_tile(fm::PassDesc* d, size_t elem, int comps, int nb, int bmax, bool exact) {
   const int packs = (d->gather == fm::G_CPLX) ? 1 : 2;
   auto fits = [&](int B, size_t cap) { return rt_lds(*d, B, elem, comps).total <= cap; };
@@ -531,11 +509,25 @@ int choose_rt_tile(fm::PassDesc* d, size_t elem, int comps, int nb, int bmax, bo
     want = (want + packs - 1) / packs * packs;
     B = std::min(B, want);
     while (B > 2 * packs && ((nb + B - 1) / B) * groups < 512) B = (B / 2 + packs - 1) / packs * packs;
-    while (B > row && !fits(B, 40960)) --B;
+    // the fused kinds run two transforms between two waits on memory and gain more from a
+    // further workgroup per CU: 320 x 250 x 180 fused FP32 714 us with 3 lines of 360 points
+    // (18 KB), 625 with 2; FP64 1138 with 3, 1043 with 2 (24 KB), 1072 with 1
+    const size_t soft = !d->fused ? 40960 : elem == 4 ? 16384 : 24576;
+    while (B > row && !fits(B, soft)) --B;
     while (B > (row + 1) / 2 && !fits(B, 81920)) --B;
   }
   while (B > 1 && !fits(B, fm::kMaxLds)) --B;
   return set_rt(d, elem, comps, B) ? FM_OK : FM_E_SIZE;
+}
+
+// A plain pass of extension or DFT length M into launch mode 6 (the runtime-length kernel
+// for a length that has a compile-time one, real-to-real types II and III with M / 2
+// points) or back out of it.  The caller tiles the pass and sets its table.
+void set_runtime(fm::PassDesc* d, int M, bool on) {
+  d->mode_rt = on;
+  const int form = runtime_form(*d);
+  if (form != fm::R2R_EXTEND) d->r2r.half = on ? form : fm::R2R_EXTEND;
+  (void)radix_plan(on && form != fm::R2R_EXTEND ? M / 2 : M, d);
 }
 
 // Largest tile (lines per workgroup) that fits the register budget and, if possible,
@@ -588,7 +580,7 @@ int wave_plain_rs(const fm::PassDesc& d, int E);
 
 bool wave_capable(const fm::PassDesc& d, size_t elem, int E) {
   // the kernels are compiled with the compile-time-length classes (fm_inst.hip)
-  if (d.force_rt || !fm::wave_length(d.M, E) || !fm::is_fast_len(d.M)) return false;
+  if (d.force_rt || d.mode_rt || !fm::wave_length(d.M, E) || !fm::is_fast_len(d.M)) return false;
   if (E == 32 && (!d.fused || d.g.curl || elem != 4)) return false;  // FP32 Poisson lines only
   if (!d.fused && d.gather == fm::G_R2R && d.out_cplx) return false;  // LDS-tile kernel only
   if (!d.fused) return wave_plain_rs(d, E) > 0;
@@ -632,11 +624,15 @@ bool wave_capable(const fm::PassDesc& d, size_t elem) {
   return wave_capable(d, elem, 16) || wave_capable(d, elem, 8);
 }
 
-// Values per lane the planner gives a fused pass in the per-wavefront kernel: 8 for
-// three-component lines when their length allows it, else 16.  Three components in FP32
-// (fused pass alone): 0.67 ms with 8 values against 0.73 with 16 at 256^3.
-int default_wave_values(const fm::PassDesc& d, size_t elem) {
-  if (d.g.curl && wave_capable(d, elem, 8)) return 8;
+// Values per lane the planner gives a fused pass of `points` points in the per-wavefront
+// kernel.  Three components: 8 when their length allows it, else 16 (FP32, fused pass
+// alone, 256^3: 0.67 ms with 8 against 0.73 with 16).  Scalar lines: 8 up to 2^23 points
+// (FP32 512-point lines of the mixed 128 x 128 x 256 workload 14.1 us with 8, 19.5 with
+// 16; small grids 3.8 with 8, 5.0 with 16), else 16 (equal at 256^3), and 32 for long FP32
+// lines in number (512^3: 1.36 ms with 32, 1.68 with 16).
+int default_wave_values(const fm::PassDesc& d, size_t elem, int64_t points) {
+  if (wave_capable(d, elem, 8) && (d.g.curl || points < (1 << 23))) return 8;
+  if (wave_capable(d, elem, 32) && d.M == 1024 && points >= (1 << 25)) return 32;
   return wave_capable(d, elem, 16) ? 16 : 8;
 }
 
@@ -770,7 +766,9 @@ hipError_t upload_vec_descs(fm_plan_s* p, hipStream_t st) {
     for (int q = 1; q < 3; ++q) {
       fm::PassDesc& d = p->vdesc[vec_slot(i, q)];
       d = p->pass[i];
+      const int half = p->pass[i].r2r.half;  // of this launch mode
       d.r2r = p->vr2r[q][vec_r2r(i)];
+      d.r2r.half = half;
       if (i == 4) {
         d.fix = p->vfix[q];
         d.has_fix = p->vhas_fix[q];
@@ -788,17 +786,23 @@ hipError_t upload_vec_descs(fm_plan_s* p, hipStream_t st) {
 // release to finish_generation.
 template <typename T>
 int make_tables_and_green(fm_plan_s* p, hipStream_t st, bool deferred) {
-  // twiddle tables for every FFT length of the passes
+  // twiddle tables for every FFT length of the passes, in both forms of the real-to-real
+  // passes that may take either
+  std::vector<int> lengths;
   for (int i = 0; i < fm_plan_s::kPasses; ++i) {
-    const int M = p->pass[i].M;
+    lengths.push_back(p->pass[i].M);
+    if (i < 5 && runtime_form(p->pass[i]) != fm::R2R_EXTEND) {
+      lengths.push_back(p->line_M[i]);
+      lengths.push_back(p->line_M[i] / 2);
+    }
+  }
+  for (const int M : lengths) {
     if (p->tw.count(M)) continue;
     void* ptr = nullptr;
     if (plan_malloc(&ptr, sizeof(T) * 2 * 5 * (size_t)M) != hipSuccess) return FM_E_NOMEM;
     p->tw[M] = ptr;
     p->table_bytes += sizeof(T) * 2 * 5 * (size_t)M;
-    int radix[fm::kRtStages];
-    const int nr = rt_schedule(M, radix);
-    FM_HIP(fm::launch_twiddles<T>(ptr, M, radix, nr, st));
+    FM_HIP(fm::launch_twiddles<T>(ptr, M, st));
   }
   for (int i = 0; i < fm_plan_s::kPasses; ++i) p->pass[i].tw = p->tw[p->pass[i].M];
   // per-stage tables of the lengths with compile-time kernels; also of a pass planned in
@@ -806,10 +810,11 @@ int make_tables_and_green(fm_plan_s* p, hipStream_t st, bool deferred) {
   // table selects the compile-time class at launch, fm_plan_s::stw_plan keeps the planned
   // choice)
   for (int i = 0; i < fm_plan_s::kPasses; ++i) {
-    const int M = p->pass[i].M;
+    const int M = p->line_M[i];
     fm::PassDesc c = p->pass[i];
+    if (c.mode_rt) set_runtime(&c, M, false);
+    const bool planned = compile_time_kernel(c, p->elem);
     c.force_rt = 0;
-    const bool planned = compile_time_kernel(p->pass[i], p->elem);
     if (!planned && !(p->force_rt[i] && wave_capable(c, p->elem))) continue;
     if (!p->stw.count(M)) {
       void* ptr = nullptr;
@@ -819,18 +824,19 @@ int make_tables_and_green(fm_plan_s* p, hipStream_t st, bool deferred) {
       p->table_bytes += sizeof(T) * 2 * n;
       FM_HIP(fm::launch_stage_twiddles<T>(ptr, M, st));
     }
-    if (planned) p->pass[i].stw = p->stw[M];
+    if (planned && !p->pass[i].mode_rt) p->pass[i].stw = p->stw[M];
+    if (planned && !p->force_rt[i]) p->stw_plan[i] = p->stw[M];
   }
-  for (int i = 0; i < fm_plan_s::kPasses; ++i) p->stw_plan[i] = p->force_rt[i] ? nullptr : p->pass[i].stw;
 
   // stage twiddles of the per-wavefront kernels (a pass may run there, now or after
   // tuning), one table per length and values per lane
   for (int i = 0; i < 5; ++i) {
     fm::PassDesc w = p->pass[i];
     w.force_rt = 0;  // the per-wavefront kernels take the compile-time length class
+    if (w.mode_rt) set_runtime(&w, p->line_M[i], false);
     for (const int E : {16, 8, 32}) {
       if (!wave_capable(w, p->elem, E)) continue;
-      const int M = p->pass[i].M;
+      const int M = p->line_M[i];
       const int key = (M << 6) | E;
       if (!p->wtw.count(key)) {
         void* ptr = nullptr;
@@ -1015,9 +1021,7 @@ int make_tables_and_green(fm_plan_s* p, hipStream_t st, bool deferred) {
     if (it == p->tw64.end()) {
       if (plan_malloc(&t64, sizeof(double) * 2 * 5 * (size_t)d.M) != hipSuccess) { rc = FM_E_NOMEM; break; }
       p->tw64[d.M] = t64;
-      int radix[fm::kRtStages];
-      const int nr = rt_schedule(d.M, radix);
-      FM_HIP(fm::launch_twiddles<double>(t64, d.M, radix, nr, st));
+      FM_HIP(fm::launch_twiddles<double>(t64, d.M, st));
     } else {
       t64 = it->second;
     }
@@ -1261,6 +1265,80 @@ bool pass_in_bounds(const fm::PassDesc& d, int64_t in_size, int64_t out_size, si
   return true;
 }
 
+// The planner's launch mode and tile of pass i, tiled so far as the LDS-tile kernel's
+// largest tile (a valid choice for every pass).  The lines between the kernels are those
+// that the tuner draws, timed on 110 grids of edges 32 ... 384 with all kinds of faces
+// (microseconds, this choice against the largest persistent tile):
+//   * real-to-real, power-of-two length: per wavefront (FP32 64-point lines 5.9 / 9.9 on
+//     32^3 points, 16.4 / 56 on 3.3 M; 512-point lines 19.7 / 50 on 3.2 M).  FP64 from
+//     2^20 points on (42.6 / 59.9 on 6.4 M; equal to a small tile below, which a batched
+//     launch can hold);
+//   * real-to-real in FP32, other lengths: the runtime-length kernel, for the types that
+//     halve there (26 / 44 on 2.4 M points, 57 / 82 on 6.3 M), else on small passes only
+//     (8.3 / 14.3 on 10^5 points; semi-unbounded type I lines 68 / 57 on 2.4 M);
+//   * packed DFT lines of 256 ... 512 points in FP32 from 2^20 points: per wavefront (256^3,
+//     65 / 90);
+//   * the other passes: one tile per workgroup with tables from global memory (FP64 inverse
+//     DFT lines: in LDS), with at most the lines per tile that leave 256 workgroups to fill
+//     the chip (FP64 64-point lines 6.4 / 7.7 on 65 k points; fused real-to-real 8.7 / 18.9
+//     on 32 k points, 89 / 180 on 3.3 M).
+void default_mode(fm_plan_s* p, int i, int comps, bool fused_r2r) {
+  fm::PassDesc& d = p->pass[i];
+  const size_t elem = p->elem;
+  const int comp_tiles = comps == 3 ? 1 : d.ncomp;
+  const int64_t lines = (int64_t)d.nb * d.nc;
+  const int packs = d.gather == fm::G_CPLX ? 1 : 2;
+  const int64_t points = lines * comp_tiles / packs * p->line_M[i];
+  fm::PassDesc w = d;
+  w.force_rt = 0;  // the per-wavefront kernels have the compile-time length class
+  if (i == 2 && wave_capable(w, elem) && !(comps == 3 && elem == 8 && lines < kCurlWaveLines64)) {
+    const int E = default_wave_values(w, elem, points);
+    for (const int W : {4, 2, 1}) {
+      if (W > 1 && (comps == 3 ? lines < kCurlWideLines : points < (1 << 25))) continue;
+      fm::PassDesc t = w;
+      if (set_wave(&t, elem, W, comp_tiles, E) && t.lds_bytes <= fm::kSoftLds) {
+        d = t;
+        return;
+      }
+    }
+  }
+  if (d.rt_n) return;
+  const bool r2r = d.gather == fm::G_R2R;
+  if (i < 5 && !d.fused && wave_capable(d, elem)) {
+    const bool wave = r2r ? elem == 4 || points >= (1 << 20)
+                          : elem == 4 && packs == 2 && d.M >= 256 && d.M <= 512 && points >= (1 << 20);
+    fm::PassDesc t = d;
+    if (wave && set_wave(&t, elem, 4, comp_tiles, d.M <= 512 ? 8 : 16) && tile_in_span_bytes(t, elem) < (int64_t(1) << 31)) {
+      d = t;
+      return;
+    }
+  } else if (i < 5 && !d.fused && r2r && elem == 4 &&
+             (runtime_form(d) != fm::R2R_EXTEND || points < (1 << 19))) {
+    fm::PassDesc t = d;
+    set_runtime(&t, p->line_M[i], true);
+    if (choose_tile(&t, elem, comps, fused_r2r, d.nb) == FM_OK) {
+      t.tiles = ((t.nb + t.B - 1) / t.B) * t.nc * comp_tiles;
+      set_magics(&t);
+      d = t;
+      return;
+    }
+  }
+  const bool inverse64 = elem == 8 && !d.fused && !r2r && d.sign > 0;
+  for (const int bmax : {64, 32, 16, 8, 4}) {
+    fm::PassDesc t = d;
+    t.persist = 0;
+    t.lds_tabs = inverse64 ? 1 : 0;
+    if (choose_tile(&t, elem, comps, fused_r2r, d.nb, bmax)) continue;
+    t.tiles = ((t.nb + t.B - 1) / t.B) * t.nc * comp_tiles;
+    set_magics(&t);
+    if (tile_in_span_bytes(t, elem) >= (int64_t(1) << 32)) continue;
+    const bool last = t.tiles >= 256 || bmax == 4 || t.B <= 4;
+    if (!last) continue;
+    d = t;
+    return;
+  }
+}
+
 int build_plan(fm_plan_s* p) {
   const bool node = p->layout == FM_NODE;
   for (int a = 0; a < 3; ++a) {
@@ -1324,9 +1402,8 @@ int build_plan(fm_plan_s* p) {
   for (int i = 0; i < 3; ++i) p->order[i] = ord[i];
   for (int i = 0; i < 3; ++i) {
     // real-to-real axes of the types II and III take FFTs of nh points instead of 2 nh in
-    // the runtime-length kernel; lengths 2 nh with a compile-time kernel keep it (they are
-    // bound by the tile's loads and stores: halving the transform of the 128-point lines
-    // of the mixed 128 x 128 x 256 workload changed no pass by more than 0.6 us of 18)
+    // the runtime-length kernel; where 2 nh has a compile-time kernel that is a matter of
+    // each pass (set_runtime)
     AxisPlan& a = p->ax[ord[i]];
     if (a.dft || a.M > fm::kMaxLen || fm::is_fast_len(a.M)) continue;  // (longer ones stay refused)
     const KindForm f = kind_form(a.fwd);
@@ -1625,7 +1702,8 @@ int build_plan(fm_plan_s* p) {
   const int line_axis[fm_plan_s::kPasses] = {a0, a1, a2, a1, a0, a2, a2};
   for (int i = 0; i < fm_plan_s::kPasses; ++i) {
     fm::PassDesc& d = p->pass[i];
-    const int rc = radix_plan(p->ax[line_axis[i]].M, &d);
+    p->line_M[i] = p->ax[line_axis[i]].M;
+    const int rc = radix_plan(p->line_M[i], &d);
     if (rc) return rc;
     const bool fused_curl = (i == 2) && curl && !p->vec3;
     d.ncomp = vec_pass(p, i) ? 1 : p->ncomp;  // launched per component
@@ -1645,22 +1723,7 @@ int build_plan(fm_plan_s* p) {
     if (rc2) return rc2;
     d.tiles = ((d.nb + d.B - 1) / d.B) * d.nc * (fused_curl ? 1 : d.ncomp);
     set_magics(&d);
-    fm::PassDesc wd = d;  // the per-wavefront kernels have the compile-time length class
-    wd.force_rt = 0;
-    const int64_t lines = (int64_t)d.nb * d.nc;
-    if (i == 2 && wave_capable(wd, p->elem) && !(fused_curl && p->elem == 8 && lines < kCurlWaveLines64)) {
-      // the per-wavefront kernel, with the most wavefronts per workgroup whose LDS stays
-      // within the preferred size
-      const int E = default_wave_values(wd, p->elem);
-      for (const int W : {4, 2, 1}) {
-        if (fused_curl && W > 1 && lines < kCurlWideLines) continue;
-        fm::PassDesc w = wd;
-        if (set_wave(&w, p->elem, W, fused_curl ? 1 : d.ncomp, E) && w.lds_bytes <= fm::kSoftLds) {
-          d = w;
-          break;
-        }
-      }
-    }
+    default_mode(p, i, comps, fused_r2r);
   }
   for (int i = 0; i < fm_plan_s::kPasses; ++i) p->pass[i].kind = pass_kind(p->pass[i]);
   const int64_t sizes_in[fm_plan_s::kPasses] = {p->Vu, p->V1, p->V2, p->vec2 ? 2 * p->V2 : p->V2, p->V1,
@@ -2279,6 +2342,7 @@ int fm_solve_batched(int count, const fm_plan* plans, const void* const* rhs_dev
 // tables (the only mode of the runtime-length and long FP64 kernels).
 int launch_mode(const fm::PassDesc& d, size_t elem) {
   if (d.wave) return d.wave == 16 ? 3 : (d.wave == 8 ? 4 : 5);
+  if (d.mode_rt) return 6;
   const bool pipelined = compile_time_kernel(d, elem) && fm::pipelined_kernel((int)elem, d.M);
   if (!pipelined || !d.lds_tabs) return 2;
   return d.persist ? 1 : 0;
@@ -2296,11 +2360,19 @@ bool retile(const fm_plan_s* p, int i, int bmax, int mode, fm::PassDesc* out) {
   const int64_t sizes_in[5] = {p->Vu, p->V1, p->V2, p->vec2 ? 2 * p->V2 : p->V2, p->V1};
   const int64_t sizes_out[5] = {p->V1, p->V2, p->V2, p->V1, p->Vu};
   d.wave = 0;
+  if (d.mode_rt || mode == 6) {
+    const bool on = mode == 6;
+    if (on && (d.fused || p->force_rt[i] || !fm::is_fast_len(p->line_M[i]))) return false;
+    set_runtime(&d, p->line_M[i], on);
+    const auto t = p->tw.find(d.M);
+    if (t == p->tw.end()) return false;
+    d.tw = t->second;
+  }
   // the per-wavefront kernel has the compile-time length; the LDS-tile kernel takes the
   // class the plan chose
-  const bool wave_mode = mode >= 3;
+  const bool wave_mode = mode >= 3 && mode <= 5;
   d.force_rt = wave_mode ? 0 : p->force_rt[i];
-  d.stw = p->stw_plan[i];
+  d.stw = mode == 6 ? nullptr : p->stw_plan[i];
   if (wave_mode) {
     // the per-wavefront kernel (16 or 8 values per lane): the most wavefronts per
     // workgroup within bmax lines; launched in the compile-time class, which the stage
@@ -2342,7 +2414,7 @@ int apply_tiling(fm_plan p, const int lines_per_tile[5], const int persist[5], h
   fm::PassDesc next[5];
   for (int i = 0; i < 5; ++i) {
     const int mode = persist[i];
-    if (lines_per_tile[i] < 1 || mode < 0 || mode > 5) return FM_E_ARG;
+    if (lines_per_tile[i] < 1 || mode < 0 || mode > 6) return FM_E_ARG;
     if (!retile(p, i, lines_per_tile[i], mode, &next[i])) return FM_E_ARG;
     // exactly the requested tiling (retile takes the largest tile up to the bound)
     if (next[i].B != lines_per_tile[i] || launch_mode(next[i], p->elem) != mode) return FM_E_ARG;
@@ -2490,8 +2562,10 @@ int fm_plan_tune(fm_plan p, void* workspace_dev, void* hip_stream) {
     he = time_pass(i, best, &best_ms);
     std::vector<std::pair<int, int>> seen{{best.B, launch_mode(best, p->elem)}};
     for (const int bmax : {64, 32, 16, 8, 4, 2, 1}) {
-      for (const int mode : {1, 0, 2, 3, 4, 5}) {
+      for (const int mode : {1, 0, 2, 3, 4, 5, 6}) {
         fm::PassDesc d;
+        // the runtime-length kernel never beat the per-wavefront one at powers of two
+        if (mode == 6 && wave_capable(p->pass[i], p->elem)) continue;
         if (he != hipSuccess || !retile(p, i, bmax, mode, &d)) continue;
         const std::pair<int, int> key{d.B, launch_mode(d, p->elem)};
         if (std::find(seen.begin(), seen.end(), key) != seen.end()) continue;

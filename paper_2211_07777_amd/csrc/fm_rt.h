@@ -226,13 +226,13 @@ __device__ __forceinline__ void rt_set(__attribute__((address_space(1))) cpx<T>*
   p[i].y = v.y;
 }
 
-// Input of the tile's lines (one component): put(l, i, value) for every element, eight
-// loads of a thread in flight.
-template <typename E, class Put>
-__device__ __forceinline__ void rt_load(const PassDesc& d, const void* in, int comp, const TileIdx& ti, const Put& put) {
+// Input of the tile's lines (one component): put(l, i, value) for every element, UN loads
+// of a thread in flight.
+template <int UN, typename E, class Put>
+__device__ __forceinline__ void rt_load_n(const PassDesc& d, const void* in, int comp, const TileIdx& ti,
+                                          const Put& put) {
   const auto* p = gptr<E>(in) + ((int64_t)comp * d.in_s_comp + (int64_t)ti.c * d.in_s_c + (int64_t)ti.b0 * d.in_s_b);
   RtWalk w(d.in_s_line == 1, d.in_n, d.mag_in, d.B, d.mag_B, d.in_s_line, d.in_s_b);
-  constexpr int UN = 8;
   const int n = d.in_n, nl = ti.nl;
   while (w.lc ? w.l < nl : w.i < n) {
     E v[UN];
@@ -251,14 +251,22 @@ __device__ __forceinline__ void rt_load(const PassDesc& d, const void* in, int c
   }
 }
 
+// Straight-line code runs about as fast as the instruction cache fills from L2 the first
+// time (some 100 ns per 64 bytes), and every launch starts with it empty: a tile with at
+// most one element per thread takes the short loop.
+template <typename E, class Put>
+__device__ __forceinline__ void rt_load(const PassDesc& d, const void* in, int comp, const TileIdx& ti, const Put& put) {
+  if (d.B * d.in_n <= (int)blockDim.x) rt_load_n<1, E>(d, in, comp, ti, put);
+  else rt_load_n<8, E>(d, in, comp, ti, put);
+}
+
 // Output of the tile's lines (one component): get(l, j) of every element, with the output
 // conventions of the batch axes if FIX (see store_tile).
-template <bool FIX, typename E, class Get>
-__device__ __forceinline__ void rt_store(const PassDesc& d, void* out, int comp, const TileIdx& ti, const Get& get) {
+template <int UN, bool FIX, typename E, class Get>
+__device__ __forceinline__ void rt_store_n(const PassDesc& d, void* out, int comp, const TileIdx& ti, const Get& get) {
   auto* p = (__attribute__((address_space(1))) E*)(out) +
             ((int64_t)comp * d.out_s_comp + (int64_t)ti.c * d.out_s_c + (int64_t)ti.b0 * d.out_s_b);
   RtWalk w(d.out_s_line == 1, d.out_n, d.mag_out, d.B, d.mag_B, d.out_s_line, d.out_s_b);
-  constexpr int UN = 4;
   const int n = d.out_n, nl = ti.nl;
   const Fixup& fx = d.fix;
   bool czero = false, cdup = false;
@@ -294,6 +302,12 @@ __device__ __forceinline__ void rt_store(const PassDesc& d, void* out, int comp,
       rt_set(p, oo[u], v[u]);
     }
   }
+}
+
+template <bool FIX, typename E, class Get>
+__device__ __forceinline__ void rt_store(const PassDesc& d, void* out, int comp, const TileIdx& ti, const Get& get) {
+  if (d.B * d.out_n <= (int)blockDim.x) rt_store_n<1, FIX, E>(d, out, comp, ti, get);
+  else rt_store_n<4, FIX, E>(d, out, comp, ti, get);
 }
 
 // f(line, slot) over the F x M slots of a tile (m = slot of the line).

@@ -1,0 +1,96 @@
+"""The planner's launch modes against the FP64 oracle on both sides of every line that it
+draws (sizes, types, precisions), and launch mode 6 (a plain pass in the runtime-length
+kernel although its length has a kernel of its own) for every kind of pass: set, solved,
+taken back.  Tolerances are those of every parity test (FP64 1e-12, FP32 1e-5 relative
+L-infinity)."""
+import numpy as np
+import pytest
+
+import oracle as O
+import paper_2211_07777_amd as F
+from gpu_common import TOL32, TOL64, check_conventions, gpu_solve, oracle_solve, rel_linf
+
+pytestmark = pytest.mark.gpu
+U, P, E, D = 3, 2, 0, 1
+PRECS = pytest.mark.parametrize("prec,tol", [(F.F64, TOL64), (F.F32, TOL32)])
+
+
+def solve_error(plan, f, ref, bc, layout):
+    u = gpu_solve(plan, f)
+    check_conventions(u, bc, layout)
+    return rel_linf(u, ref)
+
+
+# few lines; lines that fill 256 workgroups; 2^19 and 2^20 points; 256-point packed lines
+@PRECS
+@pytest.mark.parametrize("n,bc", [([32, 32, 32], [[E, E], [D, D], [E, D]]),
+                                  ([48, 32, 64], [[E, U], [D, E], [P, P]]),
+                                  ([128, 96, 32], [[E, D], [U, E], [D, D]]),
+                                  ([96, 96, 128], [[D, U], [E, E], [E, E]]),
+                                  ([128, 64, 128], [[U, U], [U, U], [E, E]]),
+                                  ([128, 128, 96], [[U, U], [P, P], [U, U]])])
+def test_defaults(n, bc, prec, tol):
+    h = [0.09, 0.1, 0.11]
+    for layout in (F.CELL, F.NODE):
+        f = np.random.default_rng(sum(n) + layout).standard_normal(O.user_shape(n, layout))
+        plan = F.Plan(n, h, bc, layout, F.CHAT2, prec)
+        err = solve_error(plan, f, oracle_solve(f, n, h, bc, layout), bc, layout)
+        t = plan.tiling()
+        plan.close()
+        assert err < tol, (n, bc, layout, t, err)
+
+
+# lengths with a compile-time kernel (32 ... 256 points); types I to IV, extensions, both DFTs
+@PRECS
+@pytest.mark.parametrize("n,bc", [([16, 32, 24], [[E, E], [D, D], [P, P]]),
+                                  ([48, 16, 32], [[E, D], [D, E], [U, U]]),
+                                  ([64, 24, 16], [[E, U], [U, D], [E, E]]),
+                                  ([32, 64, 32], [[P, P], [E, E], [U, U]]),
+                                  ([128, 32, 16], [[D, D], [U, U], [P, P]])])
+def test_mode_6(n, bc, prec, tol):
+    h = [0.09, 0.1, 0.11]
+    for layout in (F.CELL, F.NODE):
+        f = np.random.default_rng(sum(n) + layout).standard_normal(O.user_shape(n, layout))
+        ref = oracle_solve(f, n, h, bc, layout)
+        plan = F.Plan(n, h, bc, layout, F.CHAT2, prec)
+        t = plan.tiling()
+        before = gpu_solve(plan, f)
+        taken = 0
+        for lines in (1, 2, 5, 8):
+            for k in (0, 1, 3, 4):
+                b, m = list(t["lines_per_tile"]), list(t["persistent"])
+                b[k], m[k] = lines, 6
+                try:
+                    got = plan.set_tiling(b, m)
+                except F.FluxmiError:  # a length without a compile-time kernel is mode 2
+                    continue
+                assert got["persistent"][k] == 6 and got["lines_per_tile"][k] == lines
+                taken += 1
+                err = solve_error(plan, f, ref, bc, layout)
+                assert err < tol, (n, bc, layout, k, lines, err)
+        assert taken
+        assert plan.set_tiling(t["lines_per_tile"], t["persistent"]) == t
+        assert np.array_equal(gpu_solve(plan, f), before)
+        plan.close()
+
+
+# one set of faces per component: tangential faces of the even-odd axis, all its transforms
+@PRECS
+@pytest.mark.parametrize("tang,layout", [((E, E), F.CELL), ((D, D), F.NODE), ((E, D), F.CELL), ((D, E), F.NODE),
+                                         ((E, U), F.CELL), ((U, D), F.NODE), ((D, E), F.CELL), ((E, D), F.NODE)])
+def test_mode_6_components(tang, layout, prec, tol):
+    n, h = [32, 15, 12], [0.04, 0.07, 0.08]
+    swap = {E: D, D: E, U: U}
+    bc = [[[swap[b] for b in tang] if q == 0 else list(tang), [U, U], [U, U]] for q in range(3)]
+    f = np.random.default_rng(3).standard_normal((3,) + O.user_shape(n, layout))
+    ref = O.solve_vector(f, n, h, bc, layout, 0, F.BIOT_SAVART)
+    plan = F.Plan(n, h, bc, layout, F.CHAT2, prec, F.BIOT_SAVART)
+    t = plan.tiling()
+    for lines in (1, 4, 5):
+        for k in (0, 4):
+            b, m = list(t["lines_per_tile"]), list(t["persistent"])
+            b[k], m[k] = lines, 6
+            assert plan.set_tiling(b, m)["persistent"][k] == 6
+            err = rel_linf(gpu_solve(plan, f), ref)
+            assert err < tol, (k, lines, err)
+    plan.close()
