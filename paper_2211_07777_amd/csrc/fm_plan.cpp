@@ -413,6 +413,9 @@ int runtime_form(const fm::PassDesc& d) {
 // and nothing has shown it free of that fault.
 bool compile_time_kernel(const fm::PassDesc& d, size_t elem) {
   if (d.force_rt || d.mode_rt || !fm::is_fast_len(d.M)) return false;
+  // N-point real-to-real forms are the runtime-length kernel's, also where N itself has a
+  // compile-time kernel (768 points, whose extension of 1536 has none)
+  if (d.gather == fm::G_R2R && d.r2r.half) return false;
   if (!kFp32OneLaunch && elem == 4 && d.fused && d.gather == fm::G_R2R && d.M == 32) return false;
   return true;
 }
@@ -581,6 +584,7 @@ int wave_plain_rs(const fm::PassDesc& d, int E);
 bool wave_capable(const fm::PassDesc& d, size_t elem, int E) {
   // the kernels are compiled with the compile-time-length classes (fm_inst.hip)
   if (d.force_rt || d.mode_rt || !fm::wave_length(d.M, E) || !fm::is_fast_len(d.M)) return false;
+  if (d.gather == fm::G_R2R && d.r2r.half) return false;
   if (E == 32 && (!d.fused || d.g.curl || elem != 4)) return false;  // FP32 Poisson lines only
   if (!d.fused && d.gather == fm::G_R2R && d.out_cplx) return false;  // LDS-tile kernel only
   if (!d.fused) return wave_plain_rs(d, E) > 0;
@@ -2362,6 +2366,7 @@ bool retile(const fm_plan_s* p, int i, int bmax, int mode, fm::PassDesc* out) {
   d.wave = 0;
   if (d.mode_rt || mode == 6) {
     const bool on = mode == 6;
+    if (on && d.r2r.half && !d.mode_rt) return false;  // its only form
     if (on && (d.fused || p->force_rt[i] || !fm::is_fast_len(p->line_M[i]))) return false;
     set_runtime(&d, p->line_M[i], on);
     const auto t = p->tw.find(d.M);

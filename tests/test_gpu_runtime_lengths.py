@@ -73,3 +73,21 @@ def test_curl_lines_and_refusal(prec, tol):
     with pytest.raises(F.FluxmiError) as e:
         F.plan_inspect([4, 3, 700], h, bc, F.CELL, F.CHAT2, prec, F.BIOT_SAVART, 3)
     assert e.value.status == -3
+
+
+@pytest.mark.parametrize("prec,tol", [(F.F64, TOL64), (F.F32, TOL32)])
+@pytest.mark.parametrize("faces,N", [([E, E], 768), ([D, D], 768), ([E, U], 384), ([U, D], 384)])
+@pytest.mark.parametrize("axis", [0, 2])
+def test_half_length_with_a_kernel_of_its_own(axis, faces, N, prec, tol):
+    """Types II and III of 768 points: the length has a compile-time kernel, its extension of
+    1536 points has none."""
+    for others in (P, E):  # a plain pass, and among symmetric axes the first or the fused one
+        n, bc, h = [5, 6, 4], [[others, others] for _ in range(3)], [0.1, 0.11, 0.09]
+        n[axis], bc[axis], h[axis] = N, list(faces), 2.0 / N
+        f = np.random.default_rng(N + axis).standard_normal(O.user_shape(n, O.CELL))
+        plan = F.Plan(n, h, bc, F.CELL, F.CHAT2, prec)
+        t = plan.tiling()
+        assert plan.set_tiling(t["lines_per_tile"], t["persistent"])["persistent"] == t["persistent"]
+        err = rel_linf(gpu_solve(plan, f), oracle_solve(f, n, h, bc, O.CELL))
+        plan.close()
+        assert err < tol, (n, bc, err)
