@@ -264,7 +264,9 @@ int fm_plan_device_bytes(fm_plan p, size_t* bytes);
  * inverts them; lines_per_tile is then the lines of one workgroup).  Mode 5 serves the
  * fused pass of FP32 Poisson plans only.  6: a plain pass in the runtime-length kernel
  * although its length has a kernel of its own (passes of other lengths run there in any
- * case, reported as mode 2). */
+ * case, reported as mode 2).  7 and 8: real-to-real lines of types II and III as transforms
+ * of half their extension's length in the per-wavefront kernel, with 8 and 4 values per
+ * lane. */
 int fm_plan_tiling(fm_plan p, int lines_per_tile[5], int tiles[5], int persist[5]);
 
 /* Set the tiling of every pass, as fm_plan_tiling reports it (for example a tiling that

@@ -68,11 +68,11 @@ static hipError_t launch_wave_e(const PassDesc& d, const PassDesc* dev, const vo
 
 // Plain passes in the per-wavefront kernel: four wavefronts per workgroup, a persistent
 // grid of as many workgroups as can be resident at once (each loops over its tiles).
-template <int KIND, int E>
+template <int KIND, int E, bool HALF = false>
 static hipError_t launch_wave_plain_e(const PassDesc& d, const PassDesc* dev, const void* in,
                                       void* out, hipStream_t st) {
   if constexpr (wave_length(FM_MC, E) && KIND >= K_C2C_F && KIND <= K_R2R) {
-    constexpr auto kern = &wave_plain_kernel<FM_T, FM_MC, KIND, E>;
+    constexpr auto kern = &wave_plain_kernel<FM_T, FM_MC, KIND, E, HALF>;
     if (d.lds_bytes > kSoftLds) {
       const hipError_t e = allow_full_lds<kern>();
       if (e != hipSuccess) return e;
@@ -106,6 +106,10 @@ static hipError_t launch_wave(const PassDesc& d, const PassDesc* dev, const void
     if (d.wave == 8) return launch_wave_e<KIND, 8>(d, dev, in, out, st);
     if (d.wave == 32) return launch_wave_e<KIND, 32>(d, dev, in, out, st);
   } else {
+    if constexpr (KIND == K_R2R) {
+      if (d.r2r.half && d.wave == 8) return launch_wave_plain_e<KIND, 8, true>(d, dev, in, out, st);
+      if (d.r2r.half && d.wave == 4) return launch_wave_plain_e<KIND, 4, true>(d, dev, in, out, st);
+    }
     if (d.wave == 16) return launch_wave_plain_e<KIND, 16>(d, dev, in, out, st);
     if (d.wave == 8) return launch_wave_plain_e<KIND, 8>(d, dev, in, out, st);
   }

@@ -215,7 +215,7 @@ constexpr int fft_line_stride(int M) { return M + (M >> 4) + 1; }
 // 1 <= r < R, k < Ns) from a table at wave_tw_offset(M, s, E) + (r-1) Ns + k.
 constexpr int kWaveValues = 16;
 constexpr bool wave_length(int M, int E = kWaveValues) {
-  return (E == 8 || E == 16 || E == 32) && M >= 2 * E && M <= 64 * E && (M & (M - 1)) == 0;
+  return (E == 4 || E == 8 || E == 16 || E == 32) && M >= 2 * E && M <= 64 * E && (M & (M - 1)) == 0;
 }
 constexpr int wave_radix(int M, int s, int E = kWaveValues) {
   int rest = M / E;
@@ -242,6 +242,9 @@ constexpr int wave_tw_size(int M, int E = kWaveValues) {
   return wave_tw_offset(M, wave_stage_count(M, E), E);
 }
 // lines one wavefront holds (0 for lengths the per-wavefront kernels do not serve)
+// Post-twiddles of a plain real-to-real pass there: 2M entries of the 4M table, or M + 1 (an
+// even number, for the alignment of what follows) in the half form.
+constexpr int wave_post(int M, bool half) { return half ? M + 2 : 2 * M; }
 constexpr int wave_lines(int M, int E = kWaveValues) { return wave_length(M, E) ? 64 / (M / E) : 0; }
 
 // Lengths with compile-time kernels (other lengths use the runtime-length kernel).
@@ -312,7 +315,9 @@ struct PassDesc {
   int32_t force_rt;         // run in the runtime-length kernel although the length has a
                             // compile-time one (no tile of it fits the registers, e.g. three
                             // FP64 components, or the tile spans 4 GiB)
-  int32_t mode_rt;          // launch mode 6: the runtime-length kernel by choice
+  int32_t form_mode;        // launch mode that brings its own length and form of a pass: 6 (the
+                            // runtime-length kernel by choice), 7 and 8 (real-to-real types II
+                            // and III of M points, per wavefront); else 0
   int32_t g_off;
   uint64_t mag_gline;       // division by g.F_line
   int32_t lds_tabs;         // compile-time-length kernels that allow it: 1 = twiddle tables

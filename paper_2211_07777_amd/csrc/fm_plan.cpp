@@ -412,8 +412,8 @@ int runtime_form(const fm::PassDesc& d) {
 // runtime-length kernel: the compile-time one ran only in a test that faulted the GPU,
 // and nothing has shown it free of that fault.
 bool compile_time_kernel(const fm::PassDesc& d, size_t elem) {
-  if (d.force_rt || d.mode_rt || !fm::is_fast_len(d.M)) return false;
-  // N-point real-to-real forms are the runtime-length kernel's, also where N itself has a
+  if (d.force_rt || d.form_mode == 6 || !fm::is_fast_len(d.M)) return false;
+  // N-point real-to-real forms are not the LDS-tile kernels', also where N itself has a
   // compile-time kernel (768 points, whose extension of 1536 has none)
   if (d.gather == fm::G_R2R && d.r2r.half) return false;
   if (!kFp32OneLaunch && elem == 4 && d.fused && d.gather == fm::G_R2R && d.M == 32) return false;
@@ -523,14 +523,19 @@ int choose_rt_tile(fm::PassDesc* d, size_t elem, int comps, int nb, int bmax, bo
   return set_rt(d, elem, comps, B) ? FM_OK : FM_E_SIZE;
 }
 
-// A plain pass of extension or DFT length M into launch mode 6 (the runtime-length kernel
-// for a length that has a compile-time one, real-to-real types II and III with M / 2
-// points) or back out of it.  The caller tiles the pass and sets its table.
-void set_runtime(fm::PassDesc* d, int M, bool on) {
-  d->mode_rt = on;
+// A plain pass of extension or DFT length M into the length and form of a launch mode: 6 the
+// runtime-length kernel for a length that has a compile-time one, real-to-real types II and
+// III with M / 2 points; 7 and 8 those types with M / 2 points in the per-wavefront kernel of
+// 8 and 4 values per lane; other modes M points.  The caller tiles the pass and sets its
+// tables.
+void set_form(fm::PassDesc* d, int M, int mode) {
+  d->form_mode = mode >= 6 ? mode : 0;
   const int form = runtime_form(*d);
-  if (form != fm::R2R_EXTEND) d->r2r.half = on ? form : fm::R2R_EXTEND;
-  (void)radix_plan(on && form != fm::R2R_EXTEND ? M / 2 : M, d);
+  if (form != fm::R2R_EXTEND) d->r2r.half = mode >= 6 ? form : fm::R2R_EXTEND;
+  (void)radix_plan(mode >= 6 && form != fm::R2R_EXTEND ? M / 2 : M, d);
+}
+constexpr int mode_values(int mode) {  // values per lane of the per-wavefront modes, else 0
+  return mode == 3 ? 16 : mode == 4 || mode == 7 ? 8 : mode == 5 ? 32 : mode == 8 ? 4 : 0;
 }
 
 // Largest tile (lines per workgroup) that fits the register budget and, if possible,
@@ -583,8 +588,8 @@ int wave_plain_rs(const fm::PassDesc& d, int E);
 
 bool wave_capable(const fm::PassDesc& d, size_t elem, int E) {
   // the kernels are compiled with the compile-time-length classes (fm_inst.hip)
-  if (d.force_rt || d.mode_rt || !fm::wave_length(d.M, E) || !fm::is_fast_len(d.M)) return false;
-  if (d.gather == fm::G_R2R && d.r2r.half) return false;
+  if (d.force_rt || d.form_mode == 6 || !fm::wave_length(d.M, E) || !fm::is_fast_len(d.M)) return false;
+  if (d.gather == fm::G_R2R && d.r2r.half && d.form_mode < 7) return false;
   if (E == 32 && (!d.fused || d.g.curl || elem != 4)) return false;  // FP32 Poisson lines only
   if (!d.fused && d.gather == fm::G_R2R && d.out_cplx) return false;  // LDS-tile kernel only
   if (!d.fused) return wave_plain_rs(d, E) > 0;
@@ -611,11 +616,11 @@ int wave_plain_rs(const fm::PassDesc& d, int E) {
 }
 
 // LDS tables of the plain per-wavefront kernel after its FFT lines: stage twiddles; for
-// real-to-real passes the post-twiddles (2M entries of the 4M table) and M gather slots
-// (weight and source index, R2RSlot).
+// real-to-real passes the post-twiddles (wave_post entries of the 4M table) and M gather
+// slots (weight and source indices, R2RSlot).
 size_t wave_plain_tab_bytes(const fm::PassDesc& d, int E, size_t elem) {
   const bool r2r = d.gather == fm::G_R2R;
-  return (size_t)(fm::wave_tw_size(d.M, E) + (r2r ? 2 * d.M : 0)) * 2 * elem +
+  return (size_t)(fm::wave_tw_size(d.M, E) + (r2r ? fm::wave_post(d.M, d.r2r.half != 0) : 0)) * 2 * elem +
          (r2r ? (size_t)d.M * (2 * elem + 8) : 0);
 }
 
@@ -679,6 +684,7 @@ bool set_wave(fm::PassDesc* d, size_t elem, int W, int comp_tiles, int E) {
     if (total > (size_t)fm::kMaxLds) return false;
   }
   d->wave = E;
+  d->rt_n = 0;
   d->wave_rs = d->fused ? 0 : wave_plain_rs(*d, E);
   d->B = B;
   d->lds_bytes = (int)total;
@@ -784,6 +790,28 @@ hipError_t upload_vec_descs(fm_plan_s* p, hipStream_t st) {
   return e == hipSuccess ? hipStreamSynchronize(st) : e;
 }
 
+// Whether pass i may take launch modes 7 and 8: a real-to-real pass of type II or III whose
+// extension has a compile-time kernel.
+bool half_modes(const fm_plan_s* p, int i) {
+  const fm::PassDesc& d = p->pass[i];
+  return runtime_form(d) != fm::R2R_EXTEND && !p->force_rt[i] && !d.out_cplx && fm::is_fast_len(p->line_M[i]) &&
+         (!d.r2r.half || d.form_mode);
+}
+
+// The tables of a descriptor's length for the per-wavefront kernels, where they exist.
+void bind_wave_tables(const fm_plan_s* p, fm::PassDesc* d) {
+  auto table = [&](int E) -> const void* {
+    const auto t = p->wtw.find((d->M << 6) | E);
+    return t == p->wtw.end() ? nullptr : t->second;
+  };
+  d->wtw = table(16);
+  d->wtw8 = table(d->wave == 4 ? 4 : 8);
+  d->wtw32 = table(32);
+  // the stage table of the same class selects the compile-time kernels at launch; the
+  // per-wavefront ones do not read it
+  if (d->form_mode >= 7) d->stw = d->wtw8;
+}
+
 // Twiddle tables and the Green's spectrum of a plan, generated on stream st.  With
 // deferred = false the call waits for the generation and releases its temporaries; with
 // deferred = true it records p->ready after the generation instead and leaves the
@@ -816,7 +844,7 @@ int make_tables_and_green(fm_plan_s* p, hipStream_t st, bool deferred) {
   for (int i = 0; i < fm_plan_s::kPasses; ++i) {
     const int M = p->line_M[i];
     fm::PassDesc c = p->pass[i];
-    if (c.mode_rt) set_runtime(&c, M, false);
+    if (c.form_mode) set_form(&c, M, 0);
     const bool planned = compile_time_kernel(c, p->elem);
     c.force_rt = 0;
     if (!planned && !(p->force_rt[i] && wave_capable(c, p->elem))) continue;
@@ -828,7 +856,7 @@ int make_tables_and_green(fm_plan_s* p, hipStream_t st, bool deferred) {
       p->table_bytes += sizeof(T) * 2 * n;
       FM_HIP(fm::launch_stage_twiddles<T>(ptr, M, st));
     }
-    if (planned && !p->pass[i].mode_rt) p->pass[i].stw = p->stw[M];
+    if (planned && !p->pass[i].form_mode) p->pass[i].stw = p->stw[M];
     if (planned && !p->force_rt[i]) p->stw_plan[i] = p->stw[M];
   }
 
@@ -837,21 +865,22 @@ int make_tables_and_green(fm_plan_s* p, hipStream_t st, bool deferred) {
   for (int i = 0; i < 5; ++i) {
     fm::PassDesc w = p->pass[i];
     w.force_rt = 0;  // the per-wavefront kernels take the compile-time length class
-    if (w.mode_rt) set_runtime(&w, p->line_M[i], false);
-    for (const int E : {16, 8, 32}) {
+    for (int mode = 3; mode <= 8; ++mode) {
+      const int E = mode_values(mode);
+      if (!E || (mode >= 7 && !half_modes(p, i))) continue;
+      if (w.form_mode || mode >= 7) set_form(&w, p->line_M[i], mode);
       if (!wave_capable(w, p->elem, E)) continue;
-      const int M = p->line_M[i];
-      const int key = (M << 6) | E;
+      const int key = (w.M << 6) | E;
       if (!p->wtw.count(key)) {
         void* ptr = nullptr;
-        const size_t n = (size_t)std::max(1, fm::wave_tw_size(M, E));
+        const size_t n = (size_t)std::max(1, fm::wave_tw_size(w.M, E));
         if (plan_malloc(&ptr, sizeof(T) * 2 * n) != hipSuccess) return FM_E_NOMEM;
         p->wtw[key] = ptr;
         p->table_bytes += sizeof(T) * 2 * n;
-        FM_HIP(fm::launch_wave_twiddles<T>(ptr, M, E, st));
+        FM_HIP(fm::launch_wave_twiddles<T>(ptr, w.M, E, st));
       }
-      (E == 16 ? p->pass[i].wtw : (E == 8 ? p->pass[i].wtw8 : p->pass[i].wtw32)) = p->wtw[key];
     }
+    bind_wave_tables(p, &p->pass[i]);
   }
 
   // the curl's derivative factor of every DFT mode k (signed k_s) of the three directions
@@ -1277,6 +1306,10 @@ bool pass_in_bounds(const fm::PassDesc& d, int64_t in_size, int64_t out_size, si
 //     32^3 points, 16.4 / 56 on 3.3 M; 512-point lines 19.7 / 50 on 3.2 M).  FP64 from
 //     2^20 points on (42.6 / 59.9 on 6.4 M; equal to a small tile below, which a batched
 //     launch can hold);
+//     Types II and III there with half the points (256-point extensions of 4.2 M points
+//     18.7 / 20.6 in FP32, 25.8 / 30.8 in FP64; 512 points 55 / 70 on 16.8 M), with 4 values
+//     per lane to 256 points (8 hold twice the lines: 9.8 / 7.1 on 64^3) and 8 above, where
+//     4 do not reach (1024-point extensions 53 / 89);
 //   * real-to-real in FP32, other lengths: the runtime-length kernel, for the types that
 //     halve there (26 / 44 on 2.4 M points, 57 / 82 on 6.3 M), else on small passes only
 //     (8.3 / 14.3 on 10^5 points; semi-unbounded type I lines 68 / 57 on 2.4 M);
@@ -1308,6 +1341,15 @@ void default_mode(fm_plan_s* p, int i, int comps, bool fused_r2r) {
   }
   if (d.rt_n) return;
   const bool r2r = d.gather == fm::G_R2R;
+  if (i < 5 && half_modes(p, i) && (elem == 4 || points >= (1 << 20))) {
+    fm::PassDesc t = d;
+    const bool four = p->line_M[i] <= 512;
+    set_form(&t, p->line_M[i], four ? 8 : 7);
+    if (set_wave(&t, elem, 4, comp_tiles, four ? 4 : 8) && tile_in_span_bytes(t, elem) < (int64_t(1) << 31)) {
+      d = t;
+      return;
+    }
+  }
   if (i < 5 && !d.fused && wave_capable(d, elem)) {
     const bool wave = r2r ? elem == 4 || points >= (1 << 20)
                           : elem == 4 && packs == 2 && d.M >= 256 && d.M <= 512 && points >= (1 << 20);
@@ -1319,7 +1361,7 @@ void default_mode(fm_plan_s* p, int i, int comps, bool fused_r2r) {
   } else if (i < 5 && !d.fused && r2r && elem == 4 &&
              (runtime_form(d) != fm::R2R_EXTEND || points < (1 << 19))) {
     fm::PassDesc t = d;
-    set_runtime(&t, p->line_M[i], true);
+    set_form(&t, p->line_M[i], 6);
     if (choose_tile(&t, elem, comps, fused_r2r, d.nb) == FM_OK) {
       t.tiles = ((t.nb + t.B - 1) / t.B) * t.nc * comp_tiles;
       set_magics(&t);
@@ -1407,7 +1449,7 @@ int build_plan(fm_plan_s* p) {
   for (int i = 0; i < 3; ++i) {
     // real-to-real axes of the types II and III take FFTs of nh points instead of 2 nh in
     // the runtime-length kernel; where 2 nh has a compile-time kernel that is a matter of
-    // each pass (set_runtime)
+    // each pass (set_form)
     AxisPlan& a = p->ax[ord[i]];
     if (a.dft || a.M > fm::kMaxLen || fm::is_fast_len(a.M)) continue;  // (longer ones stay refused)
     const KindForm f = kind_form(a.fwd);
@@ -1770,7 +1812,7 @@ int launch_one(fm_plan_s* p, int i, const void* in, void* out, hipStream_t st) {
                  d.M, p->prec == FM_F64 ? "f64" : "f32", d.tiles, d.B, d.lds_bytes);
     std::fflush(stderr);
   }
-  if (d.wave && !(d.wave == 16 ? d.wtw : (d.wave == 8 ? d.wtw8 : d.wtw32))) return FM_E_ARG;
+  if (d.wave && !(d.wave == 16 ? d.wtw : (d.wave == 32 ? d.wtw32 : d.wtw8))) return FM_E_ARG;
   if (d.fused && d.g.curl && !(d.g.dtab_line && d.g.dtab_b && d.g.dtab_c)) return FM_E_ARG;
   auto run = [&](const fm::PassDesc& dq, const fm::PassDesc* dev, const void* iq, void* oq) {
     return (p->prec == FM_F64) ? fm::launch_pass<double>(dq, dev, iq, oq, st)
@@ -2345,8 +2387,8 @@ int fm_solve_batched(int count, const fm_plan* plans, const void* const* rhs_dev
 // tables, 0 one tile per workgroup with LDS tables, 2 one tile per workgroup with global
 // tables (the only mode of the runtime-length and long FP64 kernels).
 int launch_mode(const fm::PassDesc& d, size_t elem) {
+  if (d.form_mode) return d.form_mode;
   if (d.wave) return d.wave == 16 ? 3 : (d.wave == 8 ? 4 : 5);
-  if (d.mode_rt) return 6;
   const bool pipelined = compile_time_kernel(d, elem) && fm::pipelined_kernel((int)elem, d.M);
   if (!pipelined || !d.lds_tabs) return 2;
   return d.persist ? 1 : 0;
@@ -2355,7 +2397,8 @@ int launch_mode(const fm::PassDesc& d, size_t elem) {
 // A pass re-tiled with at most bmax lines per tile, in launch mode `mode` (1 persistent
 // with LDS tables, 0 one tile per workgroup with LDS tables, 2 one tile per workgroup
 // with global tables, 3 / 4 / 5 the per-wavefront kernels with 16 / 8 / 32 values per
-// lane);
+// lane, 6 the runtime-length kernel by choice, 7 / 8 half-length real-to-real lines per
+// wavefront with 8 / 4 values per lane);
 // false if no such tiling is valid for this plan (the compile-time-length kernels
 // address a tile with 32-bit offsets).
 bool retile(const fm_plan_s* p, int i, int bmax, int mode, fm::PassDesc* out) {
@@ -2364,27 +2407,25 @@ bool retile(const fm_plan_s* p, int i, int bmax, int mode, fm::PassDesc* out) {
   const int64_t sizes_in[5] = {p->Vu, p->V1, p->V2, p->vec2 ? 2 * p->V2 : p->V2, p->V1};
   const int64_t sizes_out[5] = {p->V1, p->V2, p->V2, p->V1, p->Vu};
   d.wave = 0;
-  if (d.mode_rt || mode == 6) {
-    const bool on = mode == 6;
-    if (on && d.r2r.half && !d.mode_rt) return false;  // its only form
-    if (on && (d.fused || p->force_rt[i] || !fm::is_fast_len(p->line_M[i]))) return false;
-    set_runtime(&d, p->line_M[i], on);
+  if (d.form_mode || mode >= 6) {
+    if (mode == 6 && (d.fused || p->force_rt[i] || !fm::is_fast_len(p->line_M[i]))) return false;
+    if (mode == 6 && d.r2r.half && !d.form_mode) return false;  // its only form
+    if (mode >= 7 && !half_modes(p, i)) return false;
+    set_form(&d, p->line_M[i], mode);
     const auto t = p->tw.find(d.M);
     if (t == p->tw.end()) return false;
     d.tw = t->second;
   }
   // the per-wavefront kernel has the compile-time length; the LDS-tile kernel takes the
   // class the plan chose
-  const bool wave_mode = mode >= 3 && mode <= 5;
-  d.force_rt = wave_mode ? 0 : p->force_rt[i];
+  const int E = mode_values(mode);
+  d.force_rt = E ? 0 : p->force_rt[i];
   d.stw = mode == 6 ? nullptr : p->stw_plan[i];
-  if (wave_mode) {
-    // the per-wavefront kernel (16 or 8 values per lane): the most wavefronts per
-    // workgroup within bmax lines; launched in the compile-time class, which the stage
-    // table selects
-    const int E = mode == 3 ? 16 : (mode == 4 ? 8 : 32);
+  if (E) {
+    // the per-wavefront kernel: the most wavefronts per workgroup within bmax lines;
+    // launched in the compile-time class, which the stage table selects
     if (!wave_capable(d, p->elem, E)) return false;
-    if (!d.stw) {
+    if (mode < 6 && !d.stw) {
       const auto t = p->stw.find(d.M);
       if (t == p->stw.end()) return false;
       d.stw = t->second;
@@ -2393,6 +2434,7 @@ bool retile(const fm_plan_s* p, int i, int bmax, int mode, fm::PassDesc* out) {
       fm::PassDesc w = d;
       const int lines = W * fm::wave_lines(d.M, E) * (d.fused ? 1 : wave_plain_pk(d));
       if (lines > bmax || !set_wave(&w, p->elem, W, fused_curl ? 1 : d.ncomp, E)) continue;
+      bind_wave_tables(p, &w);
       if (!pass_in_bounds(w, sizes_in[i], sizes_out[i], p->elem)) return false;
       *out = w;
       return true;
@@ -2419,7 +2461,7 @@ int apply_tiling(fm_plan p, const int lines_per_tile[5], const int persist[5], h
   fm::PassDesc next[5];
   for (int i = 0; i < 5; ++i) {
     const int mode = persist[i];
-    if (lines_per_tile[i] < 1 || mode < 0 || mode > 6) return FM_E_ARG;
+    if (lines_per_tile[i] < 1 || mode < 0 || mode > 8) return FM_E_ARG;
     if (!retile(p, i, lines_per_tile[i], mode, &next[i])) return FM_E_ARG;
     // exactly the requested tiling (retile takes the largest tile up to the bound)
     if (next[i].B != lines_per_tile[i] || launch_mode(next[i], p->elem) != mode) return FM_E_ARG;
@@ -2566,11 +2608,22 @@ int fm_plan_tune(fm_plan p, void* workspace_dev, void* hip_stream) {
     float best_ms = 0.f;
     he = time_pass(i, best, &best_ms);
     std::vector<std::pair<int, int>> seen{{best.B, launch_mode(best, p->elem)}};
+    fm::PassDesc form = best;
+    form.force_rt = p->force_rt[i];
+    if (form.form_mode) set_form(&form, p->line_M[i], 0);
+    const bool wave_ext = wave_capable(form, p->elem);
+    bool wave_half = half_modes(p, i);
+    if (wave_half) {
+      set_form(&form, p->line_M[i], 7);
+      wave_half = wave_capable(form, p->elem, 8);
+    }
     for (const int bmax : {64, 32, 16, 8, 4, 2, 1}) {
-      for (const int mode : {1, 0, 2, 3, 4, 5, 6}) {
+      for (const int mode : {1, 0, 2, 3, 4, 5, 6, 7, 8}) {
         fm::PassDesc d;
-        // the runtime-length kernel never beat the per-wavefront one at powers of two
-        if (mode == 6 && wave_capable(p->pass[i], p->elem)) continue;
+        // the runtime-length kernel never beat the per-wavefront one at powers of two, nor
+        // a whole extension there its half length
+        if (mode == 6 && wave_ext) continue;
+        if ((mode == 3 || mode == 4) && wave_half) continue;
         if (he != hipSuccess || !retile(p, i, bmax, mode, &d)) continue;
         const std::pair<int, int> key{d.B, launch_mode(d, p->elem)};
         if (std::find(seen.begin(), seen.end(), key) != seen.end()) continue;

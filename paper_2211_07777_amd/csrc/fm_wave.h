@@ -341,7 +341,16 @@ void wave_pass_kernel(const PassDesc* __restrict__ dp, const void* in, void* out
 // is formed once: in the strided (across-lines) walk a thread owns tile line tid mod B
 // and rows tid / B + u kThreads / B.
 // ---------------------------------------------------------------------------------
-template <typename T, int M, int KIND, int E_>
+//
+// HALF: the real-to-real types II and III with M points instead of the 2 M of their
+// symmetric extension (Makhoul's orderings, as in the runtime-length kernel): half the
+// butterflies, gather reads and slots for two more LDS reads per output.  With the same
+// values per lane the tile has twice the lines, whose prefetched input and reads in flight
+// cost registers (FP64, 8 values: 202 against 122), so 4 values per lane where the length
+// allows it.  256^3 FP32, 512-point extensions 69.6 us, half 60.4 with 8 values, 55.5 with
+// 4; 256 x 256 x 128 FP64 65.5, 50.1 and 43.0 us (3.1 TB/s); semi-unbounded lines of
+// 1024-point extensions 150 and (8 values) 84 us.
+template <typename T, int M, int KIND, int E_, bool HALF>
 struct WavePlain {
   static constexpr int E = E_;
   static constexpr int P = M / E;                         // lanes per FFT line
@@ -357,9 +366,9 @@ struct WavePlain {
   // input values per thread: B in_n / kThreads with in_n <= M + 1 (a node-centred periodic
   // line keeps its duplicate end point), or M / 2 + 1 for the packed half spectra and
   // real-to-real lines
-  static constexpr int U = KIND == K_R2C ? 2 * E + 1 : E + 1;
+  static constexpr int U = KIND == K_R2C || HALF ? 2 * E + 1 : E + 1;
   static constexpr int NTW = wave_tw_size(M, E);          // stage twiddles
-  static constexpr int NPOST = KIND == K_R2R ? 2 * M : 0; // real-to-real post-twiddles
+  static constexpr int NPOST = KIND == K_R2R ? wave_post(M, HALF) : 0;  // real-to-real post-twiddles
   static constexpr int NSLOT = KIND == K_R2R ? M : 0;     // real-to-real gather slots
 };
 
@@ -428,17 +437,37 @@ __device__ __forceinline__ void wp_commit(const Stage& r, const PassDesc& d,
 // Real-to-real gather: slot m of the symmetric extension of line pair (2f, 2f + 1) is
 // W_m (x_{2f}[s_m] + i x_{2f+1}[s_m]), with the source index s_m and the complex weight
 // W_m (end-point weight, mirror sign, pre-twiddle) the same for every line and tile:
-// a table of M entries built in LDS once per workgroup.
+// a table of M entries built in LDS once per workgroup.  The half form's slot is
+// W_m (X_{idx} - i X_{pair}) of the samples X = x_{2f} + i x_{2f+1}, an index of -1 standing
+// for a sample that is 0 (type II: always without a pair).
 template <typename T>
 struct R2RSlot {
   T wx, wy;
-  int idx, pad;
+  int idx, pair;
 };
 
-template <typename T, int M, int KIND, int E>
+// Slot m of the half form.
+template <typename T>
+__device__ __forceinline__ R2RSlot<T> half_slot(const PassDesc& d, GTab<T> tw, int m) {
+  const R2R& r = d.r2r;
+  const int nh = r.nh;
+  auto index = [&](int p) {
+    const int j = r.in_rev ? r.in_base - p : p - r.in_base;
+    return p >= r.plo && p <= r.phi && j >= 0 && j < d.in_n ? j : -1;
+  };
+  if (r.half == R2R_II) {
+    const bool odd = 2 * m >= nh;  // the odd samples, backwards, follow the even ones
+    return {odd && r.sin ? T(-1) : T(1), T(0), index(odd ? 2 * (nh - m) - 1 : 2 * m), -1};
+  }
+  const int p = r.sin ? nh - m : m;
+  const cpx<T> w = twid<T>(tw, m);
+  return {w.x, -w.y, index(p), index(nh - p)};
+}
+
+template <typename T, int M, int KIND, int E, bool HALF>
 __device__ __forceinline__ void wp_transform(const PassDesc& d, const TileIdx& ti, char* smem,
                                              const cpx<T>* ltw, const R2RSlot<T>* slots) {
-  using WP = WavePlain<T, M, KIND, E>;
+  using WP = WavePlain<T, M, KIND, E, HALF>;
   using In = typename WP::In;
   constexpr int P = WP::P, L = WP::L, PK = WP::PK;
   constexpr int S = (KIND == K_C2C_I || KIND == K_C2R) ? +1 : -1;
@@ -466,12 +495,34 @@ __device__ __forceinline__ void wp_transform(const PassDesc& d, const TileIdx& t
   } else {
     const T* r0 = raw + (2 * lf) * rs;
     const T* r1 = (2 * lf + 1 < nlw) ? r0 + rs : nullptr;
+    if constexpr (HALF) {
+      auto at = [&](int i) {
+        const cpx<T> x = {r0[i < 0 ? 0 : i], r1 ? r1[i < 0 ? 0 : i] : T(0)};
+        return i < 0 ? cpx<T>{T(0), T(0)} : x;
+      };
+      if (d.r2r.half == R2R_II) {
+#pragma unroll
+        for (int k = 0; k < E; ++k) {
+          const R2RSlot<T> sl = slots[j + P * k];
+          const cpx<T> a = at(sl.idx);
+          v[k] = cpx<T>{sl.wx * a.x, sl.wx * a.y};
+        }
+      } else {
+#pragma unroll
+        for (int k = 0; k < E; ++k) {
+          const R2RSlot<T> sl = slots[j + P * k];
+          const cpx<T> a = at(sl.idx), b = at(sl.pair);
+          v[k] = cmul(cpx<T>{a.x + b.y, a.y - b.x}, cpx<T>{sl.wx, sl.wy});
+        }
+      }
+    } else {
 #pragma unroll
     for (int k = 0; k < E; ++k) {
       const R2RSlot<T> sl = slots[j + P * k];
       const T a = r0[sl.idx];
       const T b = r1 ? r1[sl.idx] : T(0);
       v[k] = cpx<T>{a * sl.wx - b * sl.wy, a * sl.wy + b * sl.wx};
+    }
     }
   }
   wave_stages<T, M, E, 0, S>(v, j, line, ltw);
@@ -501,10 +552,10 @@ __device__ __forceinline__ void wp_put(O* o, const PassDesc& d, const TileIdx& t
   }
 }
 
-template <typename T, int M, int KIND, int E, bool FIX>
+template <typename T, int M, int KIND, int E, bool HALF, bool FIX>
 __device__ __forceinline__ void wp_store(const PassDesc& d, void* out, const TileIdx& ti,
                                          const char* smem, const cpx<T>* lpost, bool lc) {
-  using WP = WavePlain<T, M, KIND, E>;
+  using WP = WavePlain<T, M, KIND, E, HALF>;
   constexpr int SC = scatter_of(KIND);
   using O = typename std::conditional<SC == S_CPLX || SC == S_R2C2, cpx<T>, T>::type;
   constexpr int LS = WP::LS;
@@ -522,6 +573,26 @@ __device__ __forceinline__ void wp_store(const PassDesc& d, void* out, const Til
     } else if constexpr (SC == S_REAL2) {
       const cpx<T> z = buf[(l >> 1) * LS + pad16(j < M ? j : j - M)];
       return (l & 1) ? z.y : z.x;
+    } else if constexpr (HALF) {
+      const R2R& r = d.r2r;
+      const int q = r.out_rev ? r.out_base - j : j + r.out_base;
+      const bool ok = q >= r.qlo && q <= r.qhi;  // outside: the coefficient is 0
+      const int qc = ok ? q : r.qlo;
+      const cpx<T>* z = buf + (l >> 1) * LS;
+      T v;
+      if (r.half == R2R_II) {
+        // the two lines' spectra V1 = (Z_k + conj Z_{-k}) / 2, V2 = (Z_k - conj Z_{-k}) / 2i
+        const int k = r.sin ? M - qc : qc;
+        const cpx<T> a = z[pad16(k == M ? 0 : k)], b = z[pad16(k == 0 ? 0 : M - k)], w = lpost[k];
+        v = (l & 1) ? w.x * (a.y + b.y) + w.y * (a.x - b.x) : w.x * (a.x + b.x) - w.y * (a.y - b.y);
+      } else {
+        // sample n = q / 2 or M - (q + 1) / 2 of the inverse DFT, slot -n of the forward one
+        const int n = (qc & 1) ? M - ((qc + 1) >> 1) : qc >> 1;
+        const cpx<T> y = z[pad16(n ? M - n : 0)];
+        v = (l & 1) ? y.y : y.x;
+        if (r.sin && (qc & 1)) v = -v;
+      }
+      return ok ? v : T(0);
     } else {
       return scatter_r2r<T>(buf, LS, d.r2r, lpost, l, j);
     }
@@ -576,17 +647,17 @@ __device__ __forceinline__ void wp_store(const PassDesc& d, void* out, const Til
 }
 
 // Occupancy targets of the plain per-wavefront kernels that fit them without spilling:
-// FP32 with 8 values per lane four waves per SIMD (128 VGPRs), with 16 three (168); FP64
+// FP32 with 4 or 8 values per lane four waves per SIMD (128 VGPRs), with 16 three (168); FP64
 // keeps the compiler's choice.
-template <typename T, int KIND, int E>
+template <typename T, int E>
 constexpr int wave_plain_min_waves() {
-  return sizeof(T) == 4 ? (E == 8 ? 4 : 3) : 1;
+  return sizeof(T) == 4 ? (E <= 8 ? 4 : 3) : 1;
 }
 
-template <typename T, int M, int KIND, int E>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(wave_plain_min_waves<T, KIND, E>())))
+template <typename T, int M, int KIND, int E, bool HALF>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(wave_plain_min_waves<T, E>())))
 void wave_plain_kernel(const PassDesc* __restrict__ dp, const void* in, void* out) {
-  using WP = WavePlain<T, M, KIND, E>;
+  using WP = WavePlain<T, M, KIND, E, HALF>;
   using In = typename WP::In;
   extern __shared__ __align__(16) char smem[];
   const PassDesc& d = *dp;
@@ -611,14 +682,16 @@ void wave_plain_kernel(const PassDesc* __restrict__ dp, const void* in, void* ou
     }
   }
   R2RSlot<T>* slots = reinterpret_cast<R2RSlot<T>*>(lpost + WP::NPOST);
-  if constexpr (KIND == K_R2R) {
+  if constexpr (HALF) {
+    for (int m = (int)threadIdx.x; m < M; m += kThreads) slots[m] = half_slot<T>(d, gptr<cpx<T>>(d.tw), m);
+  } else if constexpr (KIND == K_R2R) {
     const GatherR2R<T, GTab<T>> g{nullptr, 0, d.in_n, 2, d.r2r, gptr<cpx<T>>(d.tw)};
     for (int m = (int)threadIdx.x; m < M; m += kThreads) {
       R2RSlot<T> sl;
       const cpx<T> w = g.weight(m, sl.idx);
       sl.wx = w.x;
       sl.wy = w.y;
-      sl.pad = 0;
+      sl.pair = -1;
       slots[m] = sl;
     }
   }
@@ -628,10 +701,10 @@ void wave_plain_kernel(const PassDesc* __restrict__ dp, const void* in, void* ou
     const int next = xcd_tile(blockIdx.x, gridDim.x, ++k, d.tiles);
     const TileIdx tn = next >= 0 ? tile_index(d, next) : ti;
     if (next >= 0) wp_fetch<WP>(r, d, in, tn, lc_in);  // in flight during the transform
-    wp_transform<T, M, KIND, E>(d, ti, smem, ltw, slots);
+    wp_transform<T, M, KIND, E, HALF>(d, ti, smem, ltw, slots);
     __syncthreads();
-    if (d.has_fix) wp_store<T, M, KIND, E, true>(d, out, ti, smem, lpost, lc_out);
-    else wp_store<T, M, KIND, E, false>(d, out, ti, smem, lpost, lc_out);
+    if (d.has_fix) wp_store<T, M, KIND, E, HALF, true>(d, out, ti, smem, lpost, lc_out);
+    else wp_store<T, M, KIND, E, HALF, false>(d, out, ti, smem, lpost, lc_out);
     if (next < 0) return;
     __syncthreads();  // the stores' LDS reads are done before the next commit
     ti = tn;

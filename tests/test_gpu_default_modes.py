@@ -1,7 +1,7 @@
 """The planner's launch modes against the FP64 oracle on both sides of every line that it
-draws (sizes, types, precisions), and launch mode 6 (a plain pass in the runtime-length
-kernel although its length has a kernel of its own) for every kind of pass: set, solved,
-taken back.  Tolerances are those of every parity test (FP64 1e-12, FP32 1e-5 relative
+draws (sizes, types, precisions), and the launch modes that bring a length of their own (6: a
+plain pass in the runtime-length kernel although its length has a kernel; 7, 8: real-to-real
+lines of types II and III of half their extension's length): set, solved, taken back.  Tolerances are those of every parity test (FP64 1e-12, FP32 1e-5 relative
 L-infinity)."""
 import numpy as np
 import pytest
@@ -94,3 +94,68 @@ def test_mode_6_components(tang, layout, prec, tol):
             err = rel_linf(gpu_solve(plan, f), ref)
             assert err < tol, (k, lines, err)
     plan.close()
+
+
+# types II and III of 32 ... 512 points, odd line counts, open ends; every mode of the lines
+@PRECS
+@pytest.mark.parametrize("n,bc", [([32, 9, 64], [[E, E], [D, D], [D, D]]),
+                                  ([7, 128, 5], [[P, P], [D, D], [U, U]]),
+                                  ([256, 5, 6], [[E, E], [U, U], [P, P]]),
+                                  ([5, 512, 3], [[U, U], [E, E], [P, P]]),
+                                  ([32, 5, 128], [[E, U], [P, P], [U, D]]),
+                                  ([64, 3, 10], [[E, D], [P, P], [P, P]]),
+                                  ([3, 64, 10], [[P, P], [D, E], [U, U]]),
+                                  ([128, 128, 5], [[U, D], [U, E], [P, P]])])
+def test_half_lines_per_wavefront(n, bc, prec, tol):
+    taken = set()
+    for layout in (F.CELL, F.NODE):
+        h = [0.09, 0.1, 0.11]
+        f = np.random.default_rng(sum(n) + layout).standard_normal(O.user_shape(n, layout))
+        ref = oracle_solve(f, n, h, bc, layout)
+        plan = F.Plan(n, h, bc, layout, F.CHAT2, prec)
+        t = plan.tiling()
+        before = gpu_solve(plan, f)
+        for mode in (7, 8):
+            for k in (0, 1, 3, 4):
+                for lines in (4, 8, 16, 32, 64, 128):
+                    b, m = list(t["lines_per_tile"]), list(t["persistent"])
+                    b[k], m[k] = lines, mode
+                    try:
+                        got = plan.set_tiling(b, m)
+                    except F.FluxmiError:
+                        continue
+                    assert got["persistent"][k] == mode and got["lines_per_tile"][k] == lines
+                    taken.add((layout, mode, k))
+                    err = solve_error(plan, f, ref, bc, layout)
+                    assert err < tol, (n, bc, layout, k, mode, lines, err)
+        assert plan.set_tiling(t["lines_per_tile"], t["persistent"]) == t
+        assert np.array_equal(gpu_solve(plan, f), before)
+        plan.close()
+    assert {mode for _, mode, _ in taken} == ({7} if 512 in n else {7, 8}), taken
+
+
+@PRECS
+@pytest.mark.parametrize("tang,layout", [((E, E), F.CELL), ((D, D), F.CELL), ((E, D), F.NODE), ((U, D), F.CELL)])
+def test_half_lines_components(tang, layout, prec, tol):
+    n, h = [64, 15, 12], [0.04, 0.07, 0.08]
+    swap = {E: D, D: E, U: U}
+    bc = [[[swap[b] for b in tang] if q == 0 else list(tang), [U, U], [U, U]] for q in range(3)]
+    f = np.random.default_rng(4).standard_normal((3,) + O.user_shape(n, layout))
+    ref = O.solve_vector(f, n, h, bc, layout, 0, F.BIOT_SAVART)
+    plan = F.Plan(n, h, bc, layout, F.CHAT2, prec, F.BIOT_SAVART)
+    t = plan.tiling()
+    taken = 0
+    for mode in (7, 8):
+        for k in (0, 4):
+            for lines in (8, 16, 32, 64, 128):
+                b, m = list(t["lines_per_tile"]), list(t["persistent"])
+                b[k], m[k] = lines, mode
+                try:
+                    plan.set_tiling(b, m)
+                except F.FluxmiError:
+                    continue
+                taken += 1
+                err = rel_linf(gpu_solve(plan, f), ref)
+                assert err < tol, (k, mode, lines, err)
+    plan.close()
+    assert taken >= 4, taken
