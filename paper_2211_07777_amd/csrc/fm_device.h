@@ -1383,13 +1383,26 @@ constexpr int min_waves_per_simd() {
   return (PIPE == 0 && !fused_of(KIND) && KIND != K_ANY) ? 3 : 1;
 }
 
+// The descriptor and the buffers of this workgroup's component (blockIdx.y; PassDesc::grid_y).
+template <typename T, int KIND>
+__device__ __forceinline__ const PassDesc& component(const PassDesc* __restrict__ dp, const void*& in, void*& out) {
+  if constexpr (KIND == K_R2R) {
+    const PassDesc& d = dp[blockIdx.y];
+    in = static_cast<const char*>(in) + (int64_t)blockIdx.y * d.in_s_comp * (int64_t)sizeof(T) * (d.in_cplx ? 2 : 1);
+    out = static_cast<char*>(out) + (int64_t)blockIdx.y * d.out_s_comp * (int64_t)sizeof(T) * (d.out_cplx ? 2 : 1);
+    return d;
+  }
+  return *dp;
+}
+
 template <typename T, int MC, int KIND, int PIPE>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(min_waves_per_simd<KIND, PIPE>())))
 void pass_kernel(const PassDesc* __restrict__ dp,
                                                         const void* in, void* out) {
   extern __shared__ __align__(16) char smem[];
-  if constexpr (PIPE && pipelined_kernel((int)sizeof(T), MC)) run_pipelined<T, MC, KIND>(*dp, in, out, smem);
-  else run_single<T, MC, KIND>(*dp, in, out, smem);
+  const PassDesc& d = component<T, KIND>(dp, in, out);
+  if constexpr (PIPE && pipelined_kernel((int)sizeof(T), MC)) run_pipelined<T, MC, KIND>(d, in, out, smem);
+  else run_single<T, MC, KIND>(d, in, out, smem);
 }
 
 }  // namespace fm

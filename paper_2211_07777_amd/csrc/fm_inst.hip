@@ -25,6 +25,12 @@ static hipError_t allow_full_lds() {
   return once;
 }
 
+// Components of a launch (PassDesc::grid_y).
+template <int KIND>
+static int grid_y(const PassDesc& d) {
+  return KIND == K_R2R && d.grid_y > 1 ? d.grid_y : 1;
+}
+
 #if FM_MC == 0
 // Any length: one workgroup per tile.
 template <int KIND>
@@ -35,7 +41,7 @@ static hipError_t launch_kind(const PassDesc& d, const PassDesc* dev, const void
     const hipError_t e = allow_full_lds<&rt_kernel<FM_T, KIND>>();
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((rt_kernel<FM_T, KIND>), dim3(d.tiles), dim3(d.rt_threads), d.lds_bytes, st, dev, in, out);
+  hipLaunchKernelGGL((rt_kernel<FM_T, KIND>), dim3(d.tiles, grid_y<KIND>(d)), dim3(d.rt_threads), d.lds_bytes, st, dev, in, out);
   return hipGetLastError();
 }
 #else
@@ -89,8 +95,9 @@ static hipError_t launch_wave_plain_e(const PassDesc& d, const PassDesc* dev, co
         cus = 256;
       resident[slot] = per_cu * cus;
     }
-    const int grid = d.tiles < resident[slot] ? d.tiles : resident[slot];
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), d.lds_bytes, st, dev, in, out);
+    const int most = resident[slot] > grid_y<KIND>(d) ? resident[slot] / grid_y<KIND>(d) : 1;
+    const int grid = d.tiles < most ? d.tiles : most;
+    hipLaunchKernelGGL(kern, dim3(grid, grid_y<KIND>(d)), dim3(kThreads), d.lds_bytes, st, dev, in, out);
     return hipGetLastError();
   } else {
     (void)d; (void)dev; (void)in; (void)out; (void)st;
@@ -148,8 +155,9 @@ static hipError_t launch_kind(const PassDesc& d, const PassDesc* dev, const void
           cus = 256;
         resident[slot] = per_cu * cus;
       }
-      const int grid = (!persistent || !d.persist || d.tiles < resident[slot]) ? d.tiles : resident[slot];
-      hipLaunchKernelGGL((pass_kernel<FM_T, FM_MC, KIND, 1>), dim3(grid), dim3(kThreads), d.lds_bytes,
+      const int most = resident[slot] > grid_y<KIND>(d) ? resident[slot] / grid_y<KIND>(d) : 1;
+      const int grid = (!persistent || !d.persist || d.tiles < most) ? d.tiles : most;
+      hipLaunchKernelGGL((pass_kernel<FM_T, FM_MC, KIND, 1>), dim3(grid, grid_y<KIND>(d)), dim3(kThreads), d.lds_bytes,
                          st, dev, in, out);
       return hipGetLastError();
     }
@@ -159,7 +167,7 @@ static hipError_t launch_kind(const PassDesc& d, const PassDesc* dev, const void
     const hipError_t e = allow_full_lds<&pass_kernel<FM_T, FM_MC, KIND, 0>>();
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((pass_kernel<FM_T, FM_MC, KIND, 0>), dim3(d.tiles), dim3(kThreads), d.lds_bytes,
+  hipLaunchKernelGGL((pass_kernel<FM_T, FM_MC, KIND, 0>), dim3(d.tiles, grid_y<KIND>(d)), dim3(kThreads), d.lds_bytes,
                      st, dev, in, out);
   return hipGetLastError();
 }

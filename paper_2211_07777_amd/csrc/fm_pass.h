@@ -315,6 +315,8 @@ struct PassDesc {
   int32_t force_rt;         // run in the runtime-length kernel although the length has a
                             // compile-time one (no tile of it fits the registers, e.g. three
                             // FP64 components, or the tile spans 4 GiB)
+  int32_t grid_y;           // descriptors of this launch, consecutive in device memory, one per
+                            // component (plain real-to-real passes); 0 counts as 1
   int32_t form_mode;        // launch mode that brings its own length and form of a pass: 6 (the
                             // runtime-length kernel by choice), 7 and 8 (real-to-real types II
                             // and III of M points, per wavefront); else 0

@@ -286,7 +286,7 @@ struct fm_plan_s {
   // symmetric or semi-unbounded axis is the first transformed (a0); passes 1 and 5 run
   // once per component, each with its own real-to-real transform (the input's kind
   // forward, the swapped kind of the output backward), on a spectrum indexed by
-  // frequency shared by the three components.  Device descriptors of components 1 and 2
+  // frequency shared by the three components.  Device descriptors of the components
   // follow the kPasses at dpass[kPasses + vec_slot(pass, comp)].
   bool vec = false;
   // a second symmetric axis (transformed by passes 2 and 4, also once per component): the
@@ -304,7 +304,7 @@ struct fm_plan_s {
   fm::R2R vr2r[3][6] = {};
   fm::Fixup vfix[3] = {};  // pass 5's output conventions per component (its faces)
   int vhas_fix[3] = {};
-  static constexpr int kVecDesc = 12;
+  static constexpr int kVecDesc = 18;
   fm::PassDesc vdesc[kVecDesc];  // host copies of the device slots (vec_slot)
 };
 
@@ -764,18 +764,19 @@ bool vec_pass(const fm_plan_s* p, int i) {
 }
 // Per-component transform of pass i (vr2r's second index).
 int vec_r2r(int i) { return i == 0 ? 0 : i == 4 ? 1 : i == 1 ? 2 : i == 3 ? 3 : i == 5 ? 4 : 5; }
-// Device slot, after the kPasses, of component q (1 or 2) of pass i of a vector plan.
-int vec_slot(int i, int q) { return 2 * vec_r2r(i) + (q - 1); }
+// Device slot, after the kPasses, of component q of pass i of a vector plan.
+int vec_slot(int i, int q) { return 3 * vec_r2r(i) + q; }
 
-// The descriptors of components 1 and 2 of the per-component passes of a vector plan,
-// rebuilt from the plan's (component 0) descriptors with their own transforms, and
-// uploaded.
+// The descriptors of the components of the per-component passes of a vector plan, rebuilt
+// from the plan's (component 0) descriptors with their own transforms, and uploaded.
 hipError_t upload_vec_descs(fm_plan_s* p, hipStream_t st) {
   for (const int i : {0, 1, 3, 4, 5, 6}) {
     if (!vec_pass(p, i)) continue;
-    for (int q = 1; q < 3; ++q) {
+    for (int q = 0; q < 3; ++q) {
       fm::PassDesc& d = p->vdesc[vec_slot(i, q)];
       d = p->pass[i];
+      d.grid_y = 3;
+      if (q == 0) continue;
       const int half = p->pass[i].r2r.half;  // of this launch mode
       d.r2r = p->vr2r[q][vec_r2r(i)];
       d.r2r.half = half;
@@ -1818,17 +1819,12 @@ int launch_one(fm_plan_s* p, int i, const void* in, void* out, hipStream_t st) {
     return (p->prec == FM_F64) ? fm::launch_pass<double>(dq, dev, iq, oq, st)
                                : fm::launch_pass<float>(dq, dev, iq, oq, st);
   };
-  hipError_t e = run(d, p->dpass + i, in, out);
-  if (vec_pass(p, i)) {
-    // the other two components, each with its own transform along the swap axis
-    const size_t es_in = p->elem * (d.in_cplx ? 2 : 1), es_out = p->elem * (d.out_cplx ? 2 : 1);
-    for (int q = 1; q < 3 && e == hipSuccess; ++q) {
-      const int slot = vec_slot(i, q);
-      e = run(p->vdesc[slot], p->dpass + fm_plan_s::kPasses + slot,
-              static_cast<const char*>(in) + (size_t)q * d.in_s_comp * es_in,
-              static_cast<char*>(out) + (size_t)q * d.out_s_comp * es_out);
-    }
-  }
+  // a vector plan: one launch for the three components, each with its own transform along
+  // the swap axis (one by one, small grids left most CUs idle three times: 64^3 FP64 nodes,
+  // 89.1 us a solve with three launches in passes 1 and 5, 66.5 with one)
+  const int slot = vec_slot(i, 0);
+  hipError_t e = vec_pass(p, i) ? run(p->vdesc[slot], p->dpass + fm_plan_s::kPasses + slot, in, out)
+                                : run(d, p->dpass + i, in, out);
   if (e == hipSuccess && sync_debug()) e = hipStreamSynchronize(st);
   if (e != hipSuccess) {
     g_last_hip = (int)e;

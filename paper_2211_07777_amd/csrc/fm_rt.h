@@ -560,7 +560,7 @@ __device__ __forceinline__ void rt_tile(const PassDesc& d, const void* in, void*
 template <typename T, int KIND>
 __global__ __launch_bounds__(kRtThreads) void rt_kernel(const PassDesc* __restrict__ dp, const void* in, void* out) {
   extern __shared__ __align__(16) char smem[];
-  const PassDesc& d = *dp;
+  const PassDesc& d = component<T, KIND>(dp, in, out);
   for (int k = 0;; ++k) {
     const int tile = xcd_tile(blockIdx.x, gridDim.x, k, d.tiles);
     if (tile < 0) return;

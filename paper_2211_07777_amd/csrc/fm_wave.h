@@ -660,7 +660,7 @@ void wave_plain_kernel(const PassDesc* __restrict__ dp, const void* in, void* ou
   using WP = WavePlain<T, M, KIND, E, HALF>;
   using In = typename WP::In;
   extern __shared__ __align__(16) char smem[];
-  const PassDesc& d = *dp;
+  const PassDesc& d = component<T, KIND>(dp, in, out);
   int k = 0;
   int tile = xcd_tile(blockIdx.x, gridDim.x, k, d.tiles);
   if (tile < 0) return;

@@ -159,3 +159,23 @@ def test_half_lines_components(tang, layout, prec, tol):
                 assert err < tol, (k, mode, lines, err)
     plan.close()
     assert taken >= 4, taken
+
+
+@PRECS
+def test_components_on_a_persistent_grid(prec, tol):
+    """The three components of a pass in one launch, each on more tiles than a third of the
+    resident workgroups."""
+    n, h = [32, 72, 72], [0.05, 0.04, 0.03]
+    bc = [[[D, D] if q == 0 else [E, E], [P, P], [P, P]] for q in range(3)]
+    f = np.random.default_rng(6).standard_normal((3,) + O.user_shape(n, F.CELL))
+    ref = O.solve_vector(f, n, h, bc, F.CELL, 0, F.BIOT_SAVART)
+    plan = F.Plan(n, h, bc, F.CELL, F.CHAT2, prec, F.BIOT_SAVART)
+    t = plan.tiling()
+    for mode, lines in ((0, 1), (1, 1), (1, 2), (2, 1), (4, None), (6, 1), (8, None)):
+        for k in (0, 4):
+            b, m = list(t["lines_per_tile"]), list(t["persistent"])
+            b[k], m[k] = lines or 64, mode
+            assert plan.set_tiling(b, m)["tiles"][k] > (682 if lines else 32)
+            err = rel_linf(gpu_solve(plan, f), ref)
+            assert err < tol, (mode, lines, k, err)
+    plan.close()
