@@ -260,6 +260,10 @@ struct fm_plan_s {
   bool force_rt[kPasses] = {};  // the pass needs the runtime-length kernel in the LDS-tile modes
   int line_M[kPasses] = {};  // FFT length of the pass outside launch mode 6
   const void* stw_plan[kPasses] = {};  // stage table of the planned kernel (null: runtime-length class)
+  // FP64 passes in the LDS-tile kernel with their largest tile, for one-launch batches (B = 0:
+  // none), while the tiling is the planner's
+  fm::PassDesc batch_pass[5] = {};
+  bool own_tiling = true;
   int ext_spec[3];
   int64_t Vspec;
   bool cplx_spec;
@@ -813,6 +817,8 @@ void bind_wave_tables(const fm_plan_s* p, fm::PassDesc* d) {
   if (d->form_mode >= 7) d->stw = d->wtw8;
 }
 
+void set_batch_tiles(fm_plan_s* p);
+
 // Twiddle tables and the Green's spectrum of a plan, generated on stream st.  With
 // deferred = false the call waits for the generation and releases its temporaries; with
 // deferred = true it records p->ready after the generation instead and leaves the
@@ -1089,6 +1095,7 @@ int make_tables_and_green(fm_plan_s* p, hipStream_t st, bool deferred) {
     if (plan_malloc(&p->dpass, nb + nv) != hipSuccess) rc = FM_E_NOMEM;
     else p->table_bytes += nb + nv;
     if (rc == FM_OK) FM_HIP(hipMemcpyAsync(p->dpass, p->pass, nb, hipMemcpyHostToDevice, st));
+    if (rc == FM_OK && p->prec == FM_F64) set_batch_tiles(p);
     if (rc == FM_OK && p->vec) FM_HIP(upload_vec_descs(p, st));
   }
   for (int i = 0; i < 3; ++i) p->GF[i] = F[i];
@@ -1908,6 +1915,16 @@ struct fm_batch_s {
 
 namespace {
 
+// Workgroups from which a one-launch group takes the largest tiles: two per CU.  64 FP64
+// solves of edges 32 ... 64 take 1116 us with them and 1317 us with the small tiles that a
+// plan of its own needs to fill the chip.
+constexpr int64_t kBatchTiles = 512;
+
+// The descriptor of pass ps of a plan in such a group.
+const fm::PassDesc& batch_tile(const fm_plan_s* p, int ps) {
+  return p->own_tiling && p->batch_pass[ps].B > 0 ? p->batch_pass[ps] : p->pass[ps];
+}
+
 // Work buffers of every request and, for FP64, the grouped descriptor tables (returned
 // in *host, to be copied to b->dev_tables before the first run).
 int build_batch(int count, const fm_plan* plans, const void* const* rhs_dev, void* const* out_dev,
@@ -1984,9 +2001,18 @@ int build_batch(int count, const fm_plan* plans, const void* const* rhs_dev, voi
     fm::PassDesc* hd = reinterpret_cast<fm::PassDesc*>(host->data() + g.off_desc);
     int* hp = reinterpret_cast<int*>(host->data() + g.off_pref);
     int acc = 0, mx = 0;
+    // a group that fills the chip with the largest tiles takes those
+    int64_t large = 0;
+    for (int j = 0; j < g.count; ++j) large += batch_tile(plans[order[g.first + j]], g.pass).tiles;
     for (int j = 0; j < g.count; ++j) {
       const int i = order[g.first + j];
       hd[j] = all[5 * (size_t)i + g.pass];
+      if (g.single < 0 && large >= kBatchTiles) {
+        const fm::PassDesc own = hd[j];
+        hd[j] = batch_tile(plans[i], g.pass);
+        hd[j].in = own.in;
+        hd[j].out = own.out;
+      }
       hp[j] = acc;
       acc += hd[j].tiles;
       mx = std::max(mx, hd[j].lds_bytes);
@@ -2452,6 +2478,22 @@ bool retile(const fm_plan_s* p, int i, int bmax, int mode, fm::PassDesc* out) {
 extern "C++" {
 namespace {
 
+// The largest tiles of the passes that one-launch batches hold.  Two real lines share an
+// FFT, so a batch equals the single solves bitwise only where both tiles pair the same
+// lines: even ones.
+void set_batch_tiles(fm_plan_s* p) {
+  for (int i = 0; i < 5; ++i) {
+    const fm::PassDesc& d = p->pass[i];
+    if (d.wave || d.rt_n) continue;
+    const bool pairs = d.gather != fm::G_CPLX;
+    if (pairs && d.B % 2) continue;
+    fm::PassDesc t;
+    if (!retile(p, i, 64, 2, &t)) continue;
+    if (pairs && t.B % 2 && (t.B == 1 || !retile(p, i, t.B - 1, 2, &t))) continue;
+    if (t.B > d.B && !(pairs && t.B % 2)) p->batch_pass[i] = t;
+  }
+}
+
 // A tiling as fm_plan_tiling reports it, validated pass by pass and applied.
 int apply_tiling(fm_plan p, const int lines_per_tile[5], const int persist[5], hipStream_t st) {
   fm::PassDesc next[5];
@@ -2463,6 +2505,7 @@ int apply_tiling(fm_plan p, const int lines_per_tile[5], const int persist[5], h
     if (next[i].B != lines_per_tile[i] || launch_mode(next[i], p->elem) != mode) return FM_E_ARG;
   }
   for (int i = 0; i < 5; ++i) p->pass[i] = next[i];
+  p->own_tiling = false;
   FM_HIP(hipMemcpyAsync(p->dpass, p->pass, sizeof(fm::PassDesc) * 5, hipMemcpyHostToDevice, st));
   FM_HIP(hipStreamSynchronize(st));
   if (p->vec) FM_HIP(upload_vec_descs(p, st));
@@ -2633,6 +2676,7 @@ int fm_plan_tune(fm_plan p, void* workspace_dev, void* hip_stream) {
       }
     }
     p->pass[i] = best;
+    p->own_tiling = false;
     if (he == hipSuccess)
       he = hipMemcpyAsync(p->dpass + i, &p->pass[i], sizeof(fm::PassDesc), hipMemcpyHostToDevice, st);
   }

@@ -179,3 +179,22 @@ def test_components_on_a_persistent_grid(prec, tol):
             err = rel_linf(gpu_solve(plan, f), ref)
             assert err < tol, (mode, lines, k, err)
     plan.close()
+
+
+def test_large_batches_equal_single_solves_bitwise():
+    """A one-launch batch that fills the chip takes larger tiles than the plans of their own."""
+    import torch
+    from paper_2211_07777_amd import workloads as W
+    reqs = W.serving_stream(count=40, qps=1e4, seed=31, edges=(32, 48, 64))
+    plans = [F.Plan(r["n"], r["h"], r["bc"], r["layout"], F.CHAT2, F.F64) for r in reqs]
+    rhs = [W.request_rhs_device(r, torch.float64) for r in reqs]
+    single = [p.solve(x).clone() for p, x in zip(plans, rhs)]
+    outs = [torch.empty_like(x) for x in rhs]
+    ws = torch.empty(F.batched_workspace_bytes(plans), dtype=torch.uint8, device="cuda")
+    batch = F.Batch(plans, rhs, outs, ws)
+    batch.run()
+    torch.cuda.synchronize()
+    batch.close()
+    for r, p, a, b in zip(reqs, plans, single, outs):
+        assert torch.equal(a, b), (r["n"], r["bc"], r["layout"])
+        p.close()
