@@ -1313,7 +1313,8 @@ bool pass_in_bounds(const fm::PassDesc& d, int64_t in_size, int64_t out_size, si
 //   * real-to-real, power-of-two length: per wavefront (FP32 64-point lines 5.9 / 9.9 on
 //     32^3 points, 16.4 / 56 on 3.3 M; 512-point lines 19.7 / 50 on 3.2 M).  FP64 from
 //     2^20 points on (42.6 / 59.9 on 6.4 M; equal to a small tile below, which a batched
-//     launch can hold);
+//     launch can hold) and in vector plans, which are not batched and launch three
+//     components at once (65^3 nodes 11.3 / 16.0);
 //     Types II and III there with half the points (256-point extensions of 4.2 M points
 //     18.7 / 20.6 in FP32, 25.8 / 30.8 in FP64; 512 points 55 / 70 on 16.8 M), with 4 values
 //     per lane to 256 points (8 hold twice the lines: 9.8 / 7.1 on 64^3) and 8 above, where
@@ -1349,7 +1350,7 @@ void default_mode(fm_plan_s* p, int i, int comps, bool fused_r2r) {
   }
   if (d.rt_n) return;
   const bool r2r = d.gather == fm::G_R2R;
-  if (i < 5 && half_modes(p, i) && (elem == 4 || points >= (1 << 20))) {
+  if (i < 5 && half_modes(p, i) && (elem == 4 || p->vec || points >= (1 << 20))) {
     fm::PassDesc t = d;
     const bool four = p->line_M[i] <= 512;
     set_form(&t, p->line_M[i], four ? 8 : 7);
@@ -1359,7 +1360,7 @@ void default_mode(fm_plan_s* p, int i, int comps, bool fused_r2r) {
     }
   }
   if (i < 5 && !d.fused && wave_capable(d, elem)) {
-    const bool wave = r2r ? elem == 4 || points >= (1 << 20)
+    const bool wave = r2r ? elem == 4 || p->vec || points >= (1 << 20)
                           : elem == 4 && packs == 2 && d.M >= 256 && d.M <= 512 && points >= (1 << 20);
     fm::PassDesc t = d;
     if (wave && set_wave(&t, elem, 4, comp_tiles, d.M <= 512 ? 8 : 16) && tile_in_span_bytes(t, elem) < (int64_t(1) << 31)) {
