@@ -1388,8 +1388,10 @@ template <typename T, int KIND>
 __device__ __forceinline__ const PassDesc& component(const PassDesc* __restrict__ dp, const void*& in, void*& out) {
   if constexpr (KIND == K_R2R) {
     const PassDesc& d = dp[blockIdx.y];
-    in = static_cast<const char*>(in) + (int64_t)blockIdx.y * d.in_s_comp * (int64_t)sizeof(T) * (d.in_cplx ? 2 : 1);
-    out = static_cast<char*>(out) + (int64_t)blockIdx.y * d.out_s_comp * (int64_t)sizeof(T) * (d.out_cplx ? 2 : 1);
+    if (blockIdx.y != 0) {
+      in = static_cast<const T*>(in) + (int64_t)blockIdx.y * (d.in_s_comp << d.in_cplx);
+      out = static_cast<T*>(out) + (int64_t)blockIdx.y * (d.out_s_comp << d.out_cplx);
+    }
     return d;
   }
   return *dp;
