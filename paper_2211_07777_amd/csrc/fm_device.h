@@ -1338,7 +1338,7 @@ template <typename T, int MC, int KIND>
 __device__ __forceinline__ void run_single(const PassDesc& d, const void* in, void* out,
                                            char* smem) {
   // tiles in the XCD-aware order; with a grid of one block per tile each block takes
-  // one or two tiles
+  // one
   using E = typename std::conditional<in_cplx_of(KIND), cpx<T>, T>::type;
   constexpr int NCL = KIND == K_F_CURL ? 3 : 1;
   constexpr int U = StageCount<T, E, NCL, MC>::U;

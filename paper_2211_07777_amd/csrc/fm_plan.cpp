@@ -258,7 +258,7 @@ struct fm_plan_s {
   static constexpr int kPasses = 7;
   fm::PassDesc pass[kPasses];
   bool force_rt[kPasses] = {};  // the pass needs the runtime-length kernel in the LDS-tile modes
-  int line_M[kPasses] = {};  // FFT length of the pass outside launch mode 6
+  int line_M[kPasses] = {};  // FFT length of the pass in launch modes 0 to 5
   const void* stw_plan[kPasses] = {};  // stage table of the planned kernel (null: runtime-length class)
   // FP64 passes in the LDS-tile kernel with their largest tile, for one-launch batches (B = 0:
   // none), while the tiling is the planner's
@@ -1829,7 +1829,8 @@ int launch_one(fm_plan_s* p, int i, const void* in, void* out, hipStream_t st) {
   };
   // a vector plan: one launch for the three components, each with its own transform along
   // the swap axis (one by one, small grids left most CUs idle three times: 64^3 FP64 nodes,
-  // 89.1 us a solve with three launches in passes 1 and 5, 66.5 with one)
+  // 89.1 us a solve with three launches in passes 1 and 5, 66.5 with one, 57.8 with
+  // those passes per wavefront)
   const int slot = vec_slot(i, 0);
   hipError_t e = vec_pass(p, i) ? run(p->vdesc[slot], p->dpass + fm_plan_s::kPasses + slot, in, out)
                                 : run(d, p->dpass + i, in, out);
@@ -1917,7 +1918,7 @@ struct fm_batch_s {
 namespace {
 
 // Workgroups from which a one-launch group takes the largest tiles: two per CU.  64 FP64
-// solves of edges 32 ... 64 take 1116 us with them and 1317 us with the small tiles that a
+// solves of edges 32 ... 64 take 1046 us with them and 1317 us with the small tiles that a
 // plan of its own needs to fill the chip.
 constexpr int64_t kBatchTiles = 512;
 

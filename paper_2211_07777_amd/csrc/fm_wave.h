@@ -296,7 +296,7 @@ __device__ __forceinline__ void wave_curl_tile(const PassDesc& d, const void* in
 }
 
 // Tiles in the XCD-aware order of the other pass kernels; a grid of one workgroup per
-// tile gives each workgroup one or two tiles.
+// tile gives each workgroup one tile.
 // Occupancy targets (waves per SIMD) that the curl kernels fit: FP32 four with 16 values per
 // lane (at most 5 dwords spilled at 1024 points) and six with 8, FP64 two and four.
 template <typename T, int KIND, int E>
