@@ -1328,9 +1328,13 @@ bool pass_in_bounds(const fm::PassDesc& d, int64_t in_size, int64_t out_size, si
 //     DFT lines: in LDS), with at most the lines per tile that leave 256 workgroups to fill
 //     the chip (FP64 64-point lines 6.4 / 7.7 on 65 k points; fused real-to-real 8.7 / 18.9
 //     on 32 k points, 89 / 180 on 3.3 M).
-void default_mode(fm_plan_s* p, int i, int comps, bool fused_r2r) {
+// A choice is taken only if it is valid for this pass (pass_in_bounds on buffers of in_size
+// and out_size elements): the per-wavefront kernels address a tile's output with 32-bit
+// offsets, which a grid of 2048 x 2048 x 512 exceeds, where the LDS-tile kernel's have 64.
+void default_mode(fm_plan_s* p, int i, int comps, bool fused_r2r, int64_t in_size, int64_t out_size) {
   fm::PassDesc& d = p->pass[i];
   const size_t elem = p->elem;
+  auto valid = [&](const fm::PassDesc& t) { return pass_in_bounds(t, in_size, out_size, elem); };
   const int comp_tiles = comps == 3 ? 1 : d.ncomp;
   const int64_t lines = (int64_t)d.nb * d.nc;
   const int packs = d.gather == fm::G_CPLX ? 1 : 2;
@@ -1342,7 +1346,7 @@ void default_mode(fm_plan_s* p, int i, int comps, bool fused_r2r) {
     for (const int W : {4, 2, 1}) {
       if (W > 1 && (comps == 3 ? lines < kCurlWideLines : points < (1 << 25))) continue;
       fm::PassDesc t = w;
-      if (set_wave(&t, elem, W, comp_tiles, E) && t.lds_bytes <= fm::kSoftLds) {
+      if (set_wave(&t, elem, W, comp_tiles, E) && t.lds_bytes <= fm::kSoftLds && valid(t)) {
         d = t;
         return;
       }
@@ -1354,7 +1358,7 @@ void default_mode(fm_plan_s* p, int i, int comps, bool fused_r2r) {
     fm::PassDesc t = d;
     const bool four = p->line_M[i] <= 512;
     set_form(&t, p->line_M[i], four ? 8 : 7);
-    if (set_wave(&t, elem, 4, comp_tiles, four ? 4 : 8) && tile_in_span_bytes(t, elem) < (int64_t(1) << 31)) {
+    if (set_wave(&t, elem, 4, comp_tiles, four ? 4 : 8) && valid(t) && tile_in_span_bytes(t, elem) < (int64_t(1) << 31)) {
       d = t;
       return;
     }
@@ -1363,7 +1367,8 @@ void default_mode(fm_plan_s* p, int i, int comps, bool fused_r2r) {
     const bool wave = r2r ? elem == 4 || p->vec || points >= (1 << 20)
                           : elem == 4 && packs == 2 && d.M >= 256 && d.M <= 512 && points >= (1 << 20);
     fm::PassDesc t = d;
-    if (wave && set_wave(&t, elem, 4, comp_tiles, d.M <= 512 ? 8 : 16) && tile_in_span_bytes(t, elem) < (int64_t(1) << 31)) {
+    if (wave && set_wave(&t, elem, 4, comp_tiles, d.M <= 512 ? 8 : 16) && valid(t) &&
+        tile_in_span_bytes(t, elem) < (int64_t(1) << 31)) {
       d = t;
       return;
     }
@@ -1374,8 +1379,10 @@ void default_mode(fm_plan_s* p, int i, int comps, bool fused_r2r) {
     if (choose_tile(&t, elem, comps, fused_r2r, d.nb) == FM_OK) {
       t.tiles = ((t.nb + t.B - 1) / t.B) * t.nc * comp_tiles;
       set_magics(&t);
-      d = t;
-      return;
+      if (valid(t)) {
+        d = t;
+        return;
+      }
     }
   }
   const bool inverse64 = elem == 8 && !d.fused && !r2r && d.sign > 0;
@@ -1386,7 +1393,7 @@ void default_mode(fm_plan_s* p, int i, int comps, bool fused_r2r) {
     if (choose_tile(&t, elem, comps, fused_r2r, d.nb, bmax)) continue;
     t.tiles = ((t.nb + t.B - 1) / t.B) * t.nc * comp_tiles;
     set_magics(&t);
-    if (tile_in_span_bytes(t, elem) >= (int64_t(1) << 32)) continue;
+    if (tile_in_span_bytes(t, elem) >= (int64_t(1) << 32) || !valid(t)) continue;
     const bool last = t.tiles >= 256 || bmax == 4 || t.B <= 4;
     if (!last) continue;
     d = t;
@@ -1755,6 +1762,9 @@ int build_plan(fm_plan_s* p) {
     }
   }
   const int line_axis[fm_plan_s::kPasses] = {a0, a1, a2, a1, a0, a2, a2};
+  const int64_t sizes_in[fm_plan_s::kPasses] = {p->Vu, p->V1, p->V2, p->vec2 ? 2 * p->V2 : p->V2, p->V1,
+                                                p->V2, p->Vspec};
+  const int64_t sizes_out[fm_plan_s::kPasses] = {p->V1, p->V2, p->V2, p->V1, p->Vu, p->Vspec, p->V2};
   for (int i = 0; i < fm_plan_s::kPasses; ++i) {
     fm::PassDesc& d = p->pass[i];
     p->line_M[i] = p->ax[line_axis[i]].M;
@@ -1778,12 +1788,9 @@ int build_plan(fm_plan_s* p) {
     if (rc2) return rc2;
     d.tiles = ((d.nb + d.B - 1) / d.B) * d.nc * (fused_curl ? 1 : d.ncomp);
     set_magics(&d);
-    default_mode(p, i, comps, fused_r2r);
+    default_mode(p, i, comps, fused_r2r, sizes_in[i], sizes_out[i]);
   }
   for (int i = 0; i < fm_plan_s::kPasses; ++i) p->pass[i].kind = pass_kind(p->pass[i]);
-  const int64_t sizes_in[fm_plan_s::kPasses] = {p->Vu, p->V1, p->V2, p->vec2 ? 2 * p->V2 : p->V2, p->V1,
-                                                p->V2, p->Vspec};
-  const int64_t sizes_out[fm_plan_s::kPasses] = {p->V1, p->V2, p->V2, p->V1, p->Vu, p->Vspec, p->V2};
   for (int i = 0; i < fm_plan_s::kPasses; ++i)
     if (!pass_in_bounds(p->pass[i], sizes_in[i], sizes_out[i], p->elem)) return FM_E_SIZE;
   return FM_OK;
