@@ -771,25 +771,27 @@ int vec_r2r(int i) { return i == 0 ? 0 : i == 4 ? 1 : i == 1 ? 2 : i == 3 ? 3 : 
 // Device slot, after the kPasses, of component q of pass i of a vector plan.
 int vec_slot(int i, int q) { return 3 * vec_r2r(i) + q; }
 
-// The descriptors of the components of the per-component passes of a vector plan, rebuilt
-// from the plan's (component 0) descriptors with their own transforms, and uploaded.
-hipError_t upload_vec_descs(fm_plan_s* p, hipStream_t st) {
-  for (const int i : {0, 1, 3, 4, 5, 6}) {
-    if (!vec_pass(p, i)) continue;
-    for (int q = 0; q < 3; ++q) {
-      fm::PassDesc& d = p->vdesc[vec_slot(i, q)];
-      d = p->pass[i];
-      d.grid_y = 3;
-      if (q == 0) continue;
-      const int half = p->pass[i].r2r.half;  // of this launch mode
-      d.r2r = p->vr2r[q][vec_r2r(i)];
-      d.r2r.half = half;
-      if (i == 4) {
-        d.fix = p->vfix[q];
-        d.has_fix = p->vhas_fix[q];
-      }
+// The descriptors of the components of pass i of a vector plan (host copies), from the
+// plan's (component 0) descriptor d of the pass, with their own transforms.
+void make_vec_descs(fm_plan_s* p, int i, const fm::PassDesc& d0) {
+  for (int q = 0; q < 3; ++q) {
+    fm::PassDesc& d = p->vdesc[vec_slot(i, q)];
+    d = d0;
+    d.grid_y = 3;
+    if (q == 0) continue;
+    d.r2r = p->vr2r[q][vec_r2r(i)];
+    d.r2r.half = d0.r2r.half;  // of this launch mode
+    if (i == 4) {
+      d.fix = p->vfix[q];
+      d.has_fix = p->vhas_fix[q];
     }
   }
+}
+
+// The descriptors of the components of all per-component passes, rebuilt and uploaded.
+hipError_t upload_vec_descs(fm_plan_s* p, hipStream_t st) {
+  for (const int i : {0, 1, 3, 4, 5, 6})
+    if (vec_pass(p, i)) make_vec_descs(p, i, p->pass[i]);
   const hipError_t e = hipMemcpyAsync(p->dpass + fm_plan_s::kPasses, p->vdesc, sizeof(p->vdesc),
                                       hipMemcpyHostToDevice, st);
   return e == hipSuccess ? hipStreamSynchronize(st) : e;
@@ -2622,15 +2624,23 @@ int fm_plan_tune(fm_plan p, void* workspace_dev, void* hip_stream) {
   // time one pass with descriptor d (uploaded to the plan's device slot): a sample is n
   // launches back to back between two events, n chosen so that a sample lasts about 0.2
   // ms (launch jitter of passes of ten microseconds would otherwise decide); best of 3
-  auto time_pass = [&](int i, const fm::PassDesc& d, float* ms) -> hipError_t {
-    hipError_t e = hipMemcpyAsync(p->dpass + i, &d, sizeof(fm::PassDesc), hipMemcpyHostToDevice, st);
+  // (a vector plan's per-component passes: one launch of the three components, as a solve
+  // makes it, which shares the chip's resident workgroups among them)
+  auto time_pass = [&](int i, const fm::PassDesc& cand, float* ms) -> hipError_t {
+    const bool vec = vec_pass(p, i);
+    const int slot = vec ? vec_slot(i, 0) : 0;
+    if (vec) make_vec_descs(p, i, cand);
+    const fm::PassDesc& d = vec ? p->vdesc[slot] : cand;
+    const fm::PassDesc* dev = p->dpass + (vec ? fm_plan_s::kPasses + slot : i);
+    hipError_t e = hipMemcpyAsync(const_cast<fm::PassDesc*>(dev), &d, sizeof(fm::PassDesc) * (vec ? 3 : 1),
+                                  hipMemcpyHostToDevice, st);
     if (e != hipSuccess) return e;
     e = hipStreamSynchronize(st);
     auto sample = [&](int n, float* t) {
       hipError_t r = hipEventRecord(e0, st);
       for (int k = 0; k < n && r == hipSuccess; ++k)
-        r = (p->prec == FM_F64) ? fm::launch_pass<double>(d, p->dpass + i, ins[i], outs[i], st)
-                                : fm::launch_pass<float>(d, p->dpass + i, ins[i], outs[i], st);
+        r = (p->prec == FM_F64) ? fm::launch_pass<double>(d, dev, ins[i], outs[i], st)
+                                : fm::launch_pass<float>(d, dev, ins[i], outs[i], st);
       if (r == hipSuccess) r = hipEventRecord(e1, st);
       if (r == hipSuccess) r = hipEventSynchronize(e1);
       if (r == hipSuccess) r = hipEventElapsedTime(t, e0, e1);
@@ -2686,11 +2696,12 @@ int fm_plan_tune(fm_plan p, void* workspace_dev, void* hip_stream) {
     }
     p->pass[i] = best;
     p->own_tiling = false;
-    if (he == hipSuccess)
-      he = hipMemcpyAsync(p->dpass + i, &p->pass[i], sizeof(fm::PassDesc), hipMemcpyHostToDevice, st);
   }
-  if (he == hipSuccess) he = hipStreamSynchronize(st);
-  if (he == hipSuccess && p->vec) he = upload_vec_descs(p, st);
+  // the device copies are those of the choices again, also after a failed timing
+  hipError_t up = hipMemcpyAsync(p->dpass, p->pass, sizeof(fm::PassDesc) * 5, hipMemcpyHostToDevice, st);
+  if (up == hipSuccess) up = hipStreamSynchronize(st);
+  if (up == hipSuccess && p->vec) up = upload_vec_descs(p, st);
+  if (he == hipSuccess) he = up;
   if (he != hipSuccess) {
     g_last_hip = (int)he;
     rc = FM_E_HIP;
