@@ -586,8 +586,7 @@ int choose_tile(fm::PassDesc* d, size_t elem, int comps, bool fused_r2r, int nb,
 // The per-wavefront fused kernel (fm_wave.h) with E values per lane: complex fused
 // passes of a power-of-two length whose lines are contiguous in memory (every fused
 // complex pass: the last axis is the fastest of its layout); three-component lines of 16
-// values per lane in FP64 only at 1024 points (one line per wavefront) and without a
-// second symmetric axis.
+// values per lane in FP64 only at 1024 points (one line per wavefront).
 int wave_plain_rs(const fm::PassDesc& d, int E);
 
 bool wave_capable(const fm::PassDesc& d, size_t elem, int E) {
@@ -598,7 +597,7 @@ bool wave_capable(const fm::PassDesc& d, size_t elem, int E) {
   if (!d.fused && d.gather == fm::G_R2R && d.out_cplx) return false;  // LDS-tile kernel only
   if (!d.fused) return wave_plain_rs(d, E) > 0;
   if (d.gather != fm::G_CPLX) return false;
-  if (d.g.curl && elem != 4 && E == 16 && (d.M != 1024 || d.g.csym_b != 0)) return false;
+  if (d.g.curl && elem != 4 && E == 16 && d.M != 1024) return false;
   return d.in_s_line == 1 && d.out_s_line == 1;
 }
 
@@ -651,7 +650,9 @@ int default_wave_values(const fm::PassDesc& d, size_t elem, int64_t points) {
 
 // FP64 three-component passes run in the per-wavefront kernel by default from this many
 // lines on: 32^3 cells (2112 lines) take 8.6 us there and 8.5 in the LDS-tile kernel, 64^3
-// (8320 lines) 21 and 29, 128^3 139 and 200.
+// (8320 lines) 21 and 29, 128^3 139 and 200.  Lines of 1024 points, which the LDS-tile
+// kernel cannot hold, always do: 40 lines 9.9 us against 17.2 in the runtime-length kernel,
+// 2112 lines 51 and 94, with two symmetric axes 25 lines 9.1 and 17.2, 8281 lines 163 and 315.
 constexpr int64_t kCurlWaveLines64 = 4096;
 // Three-component tiles of one group of lines below this many lines (many small workgroups
 // fill the chip: FP32 64^3, 12.9 us against 14.5 with two groups), of four groups above
@@ -1343,7 +1344,7 @@ void default_mode(fm_plan_s* p, int i, int comps, bool fused_r2r, int64_t in_siz
   const int64_t points = lines * comp_tiles / packs * p->line_M[i];
   fm::PassDesc w = d;
   w.force_rt = 0;  // the per-wavefront kernels have the compile-time length class
-  if (i == 2 && wave_capable(w, elem) && !(comps == 3 && elem == 8 && lines < kCurlWaveLines64)) {
+  if (i == 2 && wave_capable(w, elem) && !(comps == 3 && elem == 8 && lines < kCurlWaveLines64 && !d.rt_n)) {
     const int E = default_wave_values(w, elem, points);
     for (const int W : {4, 2, 1}) {
       if (W > 1 && (comps == 3 ? lines < kCurlWideLines : points < (1 << 25))) continue;
