@@ -650,9 +650,7 @@ int default_wave_values(const fm::PassDesc& d, size_t elem, int64_t points) {
 
 // FP64 three-component passes run in the per-wavefront kernel by default from this many
 // lines on: 32^3 cells (2112 lines) take 8.6 us there and 8.5 in the LDS-tile kernel, 64^3
-// (8320 lines) 21 and 29, 128^3 139 and 200.  Lines of 1024 points, which the LDS-tile
-// kernel cannot hold, always do: 40 lines 9.9 us against 17.2 in the runtime-length kernel,
-// 2112 lines 51 and 94, with two symmetric axes 25 lines 9.1 and 17.2, 8281 lines 163 and 315.
+// (8320 lines) 21 and 29, 128^3 139 and 200.
 constexpr int64_t kCurlWaveLines64 = 4096;
 // Three-component tiles of one group of lines below this many lines (many small workgroups
 // fill the chip: FP32 64^3, 12.9 us against 14.5 with two groups), of four groups above
@@ -1344,7 +1342,7 @@ void default_mode(fm_plan_s* p, int i, int comps, bool fused_r2r, int64_t in_siz
   const int64_t points = lines * comp_tiles / packs * p->line_M[i];
   fm::PassDesc w = d;
   w.force_rt = 0;  // the per-wavefront kernels have the compile-time length class
-  if (i == 2 && wave_capable(w, elem) && !(comps == 3 && elem == 8 && lines < kCurlWaveLines64 && !d.rt_n)) {
+  if (i == 2 && wave_capable(w, elem) && !(comps == 3 && elem == 8 && lines < kCurlWaveLines64)) {
     const int E = default_wave_values(w, elem, points);
     for (const int W : {4, 2, 1}) {
       if (W > 1 && (comps == 3 ? lines < kCurlWideLines : points < (1 << 25))) continue;
