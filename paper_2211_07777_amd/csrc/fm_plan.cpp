@@ -461,6 +461,13 @@ constexpr int kRtLongestTile = 4096;
 // Passes of fewer points than this wait on latencies more than on any throughput.
 constexpr int64_t kRtSmall = 1 << 18;
 
+// Whether a tile of `points` FFT points transforms in place in the runtime-length kernel
+// (raw_off = 0: no second buffer): the three components of a curl, whose two buffers left one
+// workgroup of five wavefronts on a CU in FP64 (3 x 840 points: 86 KB).
+bool rt_in_place(const fm::PassDesc& d, int points, int comps) {
+  return d.fused && comps == 3 && points <= 8 * fm::kRtThreads;
+}
+
 // A tile of B lines in the runtime-length kernel; false if it does not fit.
 bool set_rt(fm::PassDesc* d, size_t elem, int comps, int B) {
   const int packs = (d->gather == fm::G_CPLX) ? 1 : 2;
@@ -492,8 +499,15 @@ bool set_rt(fm::PassDesc* d, size_t elem, int comps, int B) {
   const int per = all < kRtSmall ? 2 : elem == 8 && !d->fused ? 5 : 8;
   d->rt_threads = std::max(64, std::min(fm::kRtThreads, (points / per + 63) / 64 * 64));
   d->B = B;
-  d->lds_bytes = (int)t.total;
-  d->raw_off = (int)t.raw_off;
+  // Three components transform in place, in one buffer, where eight points per thread hold
+  // them, and beyond 256 threads with the largest workgroup (its 16 wavefronts are what 128
+  // registers leave a CU): FP64 lines of 686 points 242 us with 320 threads, 198 with 448
+  // (4704 lines, 255 with two buffers).
+  const bool one = rt_in_place(*d, points, comps);
+  if (one && 8 * d->rt_threads < points) d->rt_threads += 64;
+  if (one && d->rt_threads > 256) d->rt_threads = fm::kRtThreads;
+  d->lds_bytes = (int)(one ? t.raw_off : t.total);
+  d->raw_off = one ? 0 : (int)t.raw_off;
   d->g_off = d->tab_off = 0;
   d->stw_n = d->tw_n = 0;
   return true;
@@ -1268,7 +1282,10 @@ bool pass_in_bounds(const fm::PassDesc& d, int64_t in_size, int64_t out_size, si
     }
     const RtLds t = rt_lds(d, d.B, elem, comps);
     if (prod != M || comps * M > kRtLongestTile || d.stw_n + d.tw_n != 0) return false;
-    if ((size_t)d.raw_off != t.raw_off || (size_t)d.lds_bytes < t.total || d.lds_bytes > fm::kMaxLds) return false;
+    const bool one = d.raw_off == 0;
+    if (one && (!rt_in_place(d, F * M, comps) || F * M > 8 * d.rt_threads)) return false;
+    if (!one && (size_t)d.raw_off != t.raw_off) return false;
+    if ((size_t)d.lds_bytes < (one ? t.raw_off : t.total) || d.lds_bytes > fm::kMaxLds) return false;
     if (d.rt_threads < 64 || d.rt_threads > fm::kRtThreads || d.rt_threads % 64) return false;
     const int nbt = (d.nb + d.B - 1) / d.B;
     return d.tiles == nbt * d.nc * (comps == 3 ? 1 : d.ncomp);
@@ -2022,6 +2039,12 @@ int build_batch(int count, const fm_plan* plans, const void* const* rhs_dev, voi
         hd[j] = batch_tile(plans[i], g.pass);
         hd[j].in = own.in;
         hd[j].out = own.out;
+      }
+      if (hd[j].rt_n && hd[j].raw_off == 0) {
+        // the batched kernel, whose workgroups are smaller, has no form in place
+        const RtLds t = rt_lds(hd[j], hd[j].B, plans[i]->elem, 3);
+        hd[j].raw_off = (int)t.raw_off;
+        hd[j].lds_bytes = (int)t.total;
       }
       hp[j] = acc;
       acc += hd[j].tiles;

@@ -128,9 +128,52 @@ __device__ __forceinline__ void rt_radix(const cpx<T>* __restrict__ src, cpx<T>*
   }
 }
 
+// The same stage in place, for the three components of a curl: a thread reads its
+// butterflies and writes them after a barrier.  At most 8 points per thread (the workgroup's
+// size sees to it).  A second barrier per stage, for half the LDS: FP64 lines of 840 points
+// ran one workgroup of five wavefronts per CU, now two of eight.  4704 lines of three
+// components, two buffers / in place, us: FP64 450 points 173 / 116, 840 395 / 195, 1200 440
+// / 276; FP32 450 points 98 / 89, 840 238 / 159, 1280 208 / 186.
+template <typename T, int R>
+__device__ __forceinline__ void rt_radix_in_place(cpx<T>* __restrict__ buf, int ls, int F, int MR, uint32_t mMR, int Ns,
+                                                  uint32_t mNs, GTab<T> tw) {
+  constexpr int NB = (8 + R - 1) / R;
+  const int total = F * MR;
+  cpx<T> v[NB][R];
+  int at[NB], base[NB];
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    const int u = (int)threadIdx.x + i * (int)blockDim.x;
+    at[i] = -1;
+    base[i] = 0;
+    if (u >= total) continue;
+    const int line = rt_div(u, mMR);
+    const int t = u - line * MR;
+    const int tk = rt_div(t, mNs) * Ns, k = t - tk;
+    at[i] = line * ls;
+    base[i] = tk * R + k;
+    const cpx<T>* s = buf + at[i];
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[i][r] = s[pad16(t + r * MR)];
+    if (Ns > 1) {  // uniform
+#pragma unroll
+      for (int r = 1; r < R; ++r) v[i][r] = cmul(v[i][r], twid<T>(tw, (r - 1) * Ns + k));
+    }
+    SmallDft<R, -1, T>::run(v[i]);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    if (at[i] < 0) continue;
+#pragma unroll
+    for (int q = 0; q < R; ++q) buf[at[i] + pad16(base[i] + q * Ns)] = v[i][q];
+  }
+}
+
 // Forward FFTs of the F lines in a, with b as the other buffer; returns the buffer that
-// holds the result (natural order).  Begins and ends with a barrier.
-template <typename T>
+// holds the result (natural order).  Begins and ends with a barrier.  IN_PLACE: b is not
+// used.
+template <typename T, bool IN_PLACE = false>
 __device__ __forceinline__ cpx<T>* rt_fft(const PassDesc& d, cpx<T>* a, cpx<T>* b, int ls, int F) {
   GTab<T> tw = gptr<cpx<T>>(d.tw) + 4 * d.M;
   int Ns = 1;
@@ -140,7 +183,10 @@ __device__ __forceinline__ cpx<T>* rt_fft(const PassDesc& d, cpx<T>* a, cpx<T>* 
     const int MR = d.M / R;
     const uint32_t mMR = d.rt_mr[s], mNs = d.rt_ns[s];
 #define FM_RT_CASE(RR) \
-  case RR: rt_radix<T, RR>(a, b, ls, F, MR, mMR, Ns, mNs, tw); break;
+  case RR:                                                                        \
+    if constexpr (IN_PLACE) rt_radix_in_place<T, RR>(a, ls, F, MR, mMR, Ns, mNs, tw); \
+    else rt_radix<T, RR>(a, b, ls, F, MR, mMR, Ns, mNs, tw);                      \
+    break;
     switch (R) {
       FM_RT_CASE(2)
       FM_RT_CASE(3)
@@ -159,9 +205,11 @@ __device__ __forceinline__ cpx<T>* rt_fft(const PassDesc& d, cpx<T>* a, cpx<T>* 
 #undef FM_RT_CASE
     tw += (R - 1) * Ns;
     Ns *= R;
-    cpx<T>* const x = a;
-    a = b;
-    b = x;
+    if constexpr (!IN_PLACE) {
+      cpx<T>* const x = a;
+      a = b;
+      b = x;
+    }
     __syncthreads();
   }
   return a;
@@ -395,7 +443,8 @@ __device__ __forceinline__ T rt_r2r_out(const cpx<T>* buf, int ls, const R2R& r,
 }
 
 // One tile.  KIND K_ANY reads the kind from the descriptor.  LDS: buffer a at 0, buffer b
-// (which first holds the raw lines of the kinds that gather) at raw_off.
+// (which first holds the raw lines of the kinds that gather) at raw_off; raw_off = 0: buffer
+// a alone (three components, rt_radix_in_place).
 template <typename T, int KIND>
 __device__ __forceinline__ void rt_tile(const PassDesc& d, const void* in, void* out, int tile, char* smem) {
   const int kind = KIND == K_ANY ? d.kind : KIND;
@@ -458,7 +507,8 @@ __device__ __forceinline__ void rt_tile(const PassDesc& d, const void* in, void*
     const R2RLine g{d.r2r, n};
     rt_slots(pairs, M, d.rt_mM, [&](int f, int m) { a[f * ls + pad16(m)] = rt_r2r_slot<T>(g, tw, b + f * rsp, m); });
   }
-  cpx<T>* z = rt_fft<T>(d, a, b, ls, pairs);
+  const bool one = KIND == K_F_CURL && d.raw_off == 0;  // in place (uniform)
+  cpx<T>* z = one ? rt_fft<T, KIND == K_F_CURL>(d, a, b, ls, pairs) : rt_fft<T>(d, a, b, ls, pairs);
 
   // ---- fused: times the Green's spectrum (and the curl), inverse transform
   const bool fused = fused_of(kind);
@@ -516,7 +566,7 @@ __device__ __forceinline__ void rt_tile(const PassDesc& d, const void* in, void*
       const R2RLine g{d.r2r2, ns};
       rt_slots(pairs, M, d.rt_mM, [&](int f, int m) { z[f * ls + pad16(m)] = rt_r2r_slot<T>(g, tw, y + f * ssp, m); });
     }
-    z = rt_fft<T>(d, z, z == a ? b : a, ls, pairs);
+    z = one ? rt_fft<T, KIND == K_F_CURL>(d, z, z, ls, pairs) : rt_fft<T>(d, z, z == a ? b : a, ls, pairs);
   }
 
   // ---- output
