@@ -1376,11 +1376,22 @@ __device__ __forceinline__ void run_single(const PassDesc& d, const void* in, vo
 // PIPE = 1: the pipelined kernel, with the twiddle tables staged in LDS (a persistent
 // grid, or one tile per workgroup); PIPE = 0: one tile per workgroup with the tables read
 // from global memory, which leaves LDS for more workgroups per CU.  The plain kinds of
-// the latter are held to at most 168 VGPRs (three waves per SIMD), which they fit
-// without spilling; the fused kinds would spill there and keep the compiler's choice.
-template <int KIND, int PIPE>
+// the latter are held to 168 VGPRs (three waves per SIMD) where they fit those without
+// spilling (at most 17 dwords); the fused kinds would spill there and keep the compiler's
+// choice.  Lengths with a factor 3 spill 22-98 dwords in FP32 (24 in the 96-point inverse,
+// which is still faster so), 17-28 in the forward lines of 384 and 768 points in FP64, and
+// get two waves: three components of 192^3 in FP32, packed forward lines 102 -> 66 us, complex
+// 98 -> 58, packed inverse 117 -> 78; 384 x 384 x 96 in FP64, complex forward lines 106 -> 69,
+// packed 99 -> 70.  FP64 real-to-real lines are faster with three waves and 22 dwords spilled.
+template <typename T, int MC, int KIND, int PIPE>
 constexpr int min_waves_per_simd() {
-  return (PIPE == 0 && !fused_of(KIND) && KIND != K_ANY) ? 3 : 1;
+  if (PIPE != 0 || fused_of(KIND) || KIND == K_ANY) return 1;
+  if (MC % 3 != 0 || MC < 96) return 3;
+  if (sizeof(T) == 8) return (KIND == K_C2C_F || KIND == K_R2C) && MC >= 384 ? 2 : 3;
+  if (KIND == K_C2C_F || KIND == K_R2R) return 2;
+  if (KIND == K_R2C) return MC <= 384 ? 2 : 3;
+  if (KIND == K_C2R) return MC <= 192 ? 2 : 3;
+  return 3;
 }
 
 // The descriptor and the buffers of this workgroup's component (blockIdx.y; PassDesc::grid_y).
@@ -1398,7 +1409,7 @@ __device__ __forceinline__ const PassDesc& component(const PassDesc* __restrict_
 }
 
 template <typename T, int MC, int KIND, int PIPE>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(min_waves_per_simd<KIND, PIPE>())))
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(min_waves_per_simd<T, MC, KIND, PIPE>())))
 void pass_kernel(const PassDesc* __restrict__ dp,
                                                         const void* in, void* out) {
   extern __shared__ __align__(16) char smem[];
