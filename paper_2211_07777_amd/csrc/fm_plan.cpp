@@ -1324,6 +1324,63 @@ bool pass_in_bounds(const fm::PassDesc& d, int64_t in_size, int64_t out_size, si
   return true;
 }
 
+// Bytes of a pass of `lines` packed FP32 lines beyond which the persistent kernel streams
+// better than any other: the memory-side cache.
+constexpr int64_t kCacheBytes = int64_t(1) << 28;
+bool beyond_cache(const fm::PassDesc& d, int64_t lines) {
+  return lines * 4 * ((int64_t)d.in_n * (d.in_cplx ? 2 : 1) + (int64_t)d.out_n * (d.out_cplx ? 2 : 1)) >= kCacheBytes;
+}
+
+// Whether packed FP32 DFT lines (2 real lines a transform) run per wavefront: strided lines
+// of 256 and 512 points (time over that of the persistent LDS-tile kernel 0.54-0.90),
+// contiguous ones of 512 (inverse 0.55-0.96; forward 0.65-0.91, but 1.06-1.29 beyond the
+// cache).  Contiguous lines of 256 points are better with one tile per workgroup (0.56-1.01,
+// per wavefront 0.67-1.36).
+bool packed_wave(const fm::PassDesc& d, int64_t lines) {
+  const bool forward = d.gather == fm::G_REAL2;
+  if (d.M < 256 || d.M > 512) return false;
+  if ((forward ? d.in_s_line : d.out_s_line) != 1) return true;
+  return d.M == 512 && !(forward && beyond_cache(d, lines));
+}
+
+// The launch mode with twiddle tables in LDS (1 persistent, 0 one tile per workgroup) of an
+// LDS-tile pass that is slower with them in global memory, else -1.  Per class of passes,
+// times with the tables in global memory over those of the persistent kernel (over mode 0
+// where it says so), 1552 passes of grids of edges 32 ... 384:
+//   * inverse lines with a factor 3 in FP32: complex, to 384 points, 0.82-1.17 (mode 0
+//     0.64-1.01); packed, 96 and 192 points, 0.94-1.34; packed, 384 and 768 points, 0.79-1.24
+//     (mode 0 0.67-1.10);
+//   * packed forward lines of 512 points in FP32 beyond the cache: 1.30-1.47;
+//   * forward complex lines of 384 and 768 points in FP64: 0.77-1.16 (mode 0 0.64-1.09);
+//   * 256-point inverse complex lines in FP32, 1024 ... 4096 tiles: 1.04-1.15 (0.93 at 6192);
+//   * extensions of types II to IV in FP64, 384 points, 2048 and more tiles: 0.93-1.17, 768
+//     points, 16384 and more tiles: 1.05;
+//   * fused passes of 512 and more tiles: FP32 complex and curl lines (a factor 3; the others
+//     run per wavefront) 0.94-1.23; FP64 curl lines of 128 points and more 0.99-1.30; packed
+//     real lines, FP32 to 256 points (not 192: 0.62) 1.04-1.10, FP64 below 128 0.95-1.19 (at 128
+//     0.83); FP32 real-to-real to 256 points with no factor 3 (those 0.53-0.73) 1.02-1.14.
+int lds_table_mode(const fm::PassDesc& d, size_t elem) {
+  if (d.rt_n) return -1;
+  const int M = d.M, tiles = d.tiles;
+  const bool f32 = elem == 4, three = M % 3 == 0;
+  switch (pass_kind(d)) {
+    case fm::K_C2C_I:
+      if (f32 && three && M >= 96 && M <= 384) return 0;
+      return f32 && M == 256 && tiles >= 1024 && tiles <= 4096 ? 1 : -1;
+    case fm::K_C2R: return f32 && three && M >= 96 ? (M <= 192 ? 1 : 0) : -1;
+    case fm::K_R2C: return f32 && M == 512 && beyond_cache(d, (int64_t)d.nb * d.nc * d.ncomp) ? 1 : -1;
+    case fm::K_C2C_F: return !f32 && three && M >= 384 ? 0 : -1;
+    case fm::K_R2R:
+      if (f32 || !three || !(d.r2r.a2 || d.r2r.b2)) return -1;
+      return (M == 384 && tiles >= 2048) || (M == 768 && tiles >= 16384) ? 1 : -1;
+    case fm::K_F_C2C: return f32 && tiles >= 512 ? 1 : -1;
+    case fm::K_F_CURL: return (f32 || M >= 128) && tiles >= 512 ? 1 : -1;
+    case fm::K_F_R2C: return (f32 ? M <= 256 && M != 192 : M < 128) && tiles >= 512 ? 1 : -1;
+    case fm::K_F_R2R: return f32 && !three && M <= 256 && tiles >= 512 ? 1 : -1;
+    default: return -1;
+  }
+}
+
 // The planner's launch mode and tile of pass i, tiled so far as the LDS-tile kernel's
 // largest tile (a valid choice for every pass).  The lines between the kernels are those
 // that the tuner draws, timed on 110 grids of edges 32 ... 384 with all kinds of faces
@@ -1340,8 +1397,8 @@ bool pass_in_bounds(const fm::PassDesc& d, int64_t in_size, int64_t out_size, si
 //   * real-to-real in FP32, other lengths: the runtime-length kernel, for the types that
 //     halve there (26 / 44 on 2.4 M points, 57 / 82 on 6.3 M), else on small passes only
 //     (8.3 / 14.3 on 10^5 points; semi-unbounded type I lines 68 / 57 on 2.4 M);
-//   * packed DFT lines of 256 ... 512 points in FP32 from 2^20 points: per wavefront (256^3,
-//     65 / 90);
+//   * packed DFT lines of 256 and 512 points in FP32 from 2^20 points: per wavefront
+//     (packed_wave);
 //   * the other passes: one tile per workgroup with tables from global memory (FP64 inverse
 //     DFT lines: in LDS), with at most the lines per tile that leave 256 workgroups to fill
 //     the chip (FP64 64-point lines 6.4 / 7.7 on 65 k points; fused real-to-real 8.7 / 18.9
@@ -1383,7 +1440,7 @@ void default_mode(fm_plan_s* p, int i, int comps, bool fused_r2r, int64_t in_siz
   }
   if (i < 5 && !d.fused && wave_capable(d, elem)) {
     const bool wave = r2r ? elem == 4 || p->vec || points >= (1 << 20)
-                          : elem == 4 && packs == 2 && d.M >= 256 && d.M <= 512 && points >= (1 << 20);
+                          : elem == 4 && packs == 2 && points >= (1 << 20) && packed_wave(d, lines * comp_tiles);
     fm::PassDesc t = d;
     if (wave && set_wave(&t, elem, 4, comp_tiles, d.M <= 512 ? 8 : 16) && valid(t) &&
         tile_in_span_bytes(t, elem) < (int64_t(1) << 31)) {
@@ -1405,16 +1462,21 @@ void default_mode(fm_plan_s* p, int i, int comps, bool fused_r2r, int64_t in_siz
   }
   const bool inverse64 = elem == 8 && !d.fused && !r2r && d.sign > 0;
   for (const int bmax : {64, 32, 16, 8, 4}) {
-    fm::PassDesc t = d;
-    t.persist = 0;
-    t.lds_tabs = inverse64 ? 1 : 0;
-    if (choose_tile(&t, elem, comps, fused_r2r, d.nb, bmax)) continue;
-    t.tiles = ((t.nb + t.B - 1) / t.B) * t.nc * comp_tiles;
-    set_magics(&t);
-    if (tile_in_span_bytes(t, elem) >= (int64_t(1) << 32) || !valid(t)) continue;
+    auto tiled = [&](int mode, fm::PassDesc* t) {
+      *t = d;
+      t->persist = mode == 1;
+      t->lds_tabs = mode != 2;
+      if (choose_tile(t, elem, comps, fused_r2r, d.nb, bmax)) return false;
+      t->tiles = ((t->nb + t->B - 1) / t->B) * t->nc * comp_tiles;
+      set_magics(t);
+      return tile_in_span_bytes(*t, elem) < (int64_t(1) << 32) && valid(*t);
+    };
+    fm::PassDesc t, l;
+    if (!tiled(inverse64 ? 0 : 2, &t)) continue;
     const bool last = t.tiles >= 256 || bmax == 4 || t.B <= 4;
     if (!last) continue;
-    d = t;
+    const int mode = lds_table_mode(t, elem);
+    d = mode >= 0 && tiled(mode, &l) ? l : t;
     return;
   }
 }
