@@ -260,7 +260,7 @@ struct fm_plan_s {
   bool force_rt[kPasses] = {};  // the pass needs the runtime-length kernel in the LDS-tile modes
   int line_M[kPasses] = {};  // FFT length of the pass in launch modes 0 to 5
   const void* stw_plan[kPasses] = {};  // stage table of the planned kernel (null: runtime-length class)
-  // FP64 passes in the LDS-tile kernel with their largest tile, for one-launch batches (B = 0:
+  // FP64 passes outside the per-wavefront kernels with their largest tile, for one-launch batches (B = 0:
   // none), while the tiling is the planner's
   fm::PassDesc batch_pass[5] = {};
   bool own_tiling = true;
@@ -516,8 +516,8 @@ bool set_rt(fm::PassDesc* d, size_t elem, int comps, int B) {
 // The planner's tile of the runtime-length kernel: rows of at least 64 bytes on the side
 // that is strided, at least 1024 points, within an LDS size that leaves room for several
 // workgroups on a CU (more for long lines, down to half the rows); smaller while the pass
-// has too few workgroups to fill the chip.
-int choose_rt_tile(fm::PassDesc* d, size_t elem, int comps, int nb, int bmax, bool exact) {
+// has too few workgroups to fill the chip (fill; a batch has more passes to fill it with).
+int choose_rt_tile(fm::PassDesc* d, size_t elem, int comps, int nb, int bmax, bool exact, bool fill = true) {
   const int packs = (d->gather == fm::G_CPLX) ? 1 : 2;
   auto fits = [&](int B, size_t cap) { return rt_lds(*d, B, elem, comps).total <= cap; };
   int B = std::max(1, std::min(bmax, nb));
@@ -529,7 +529,7 @@ int choose_rt_tile(fm::PassDesc* d, size_t elem, int comps, int nb, int bmax, bo
     int want = std::max(row, (1024 * packs + comps * d->M - 1) / (comps * d->M));
     want = (want + packs - 1) / packs * packs;
     B = std::min(B, want);
-    while (B > 2 * packs && ((nb + B - 1) / B) * groups < 512) B = (B / 2 + packs - 1) / packs * packs;
+    while (fill && B > 2 * packs && ((nb + B - 1) / B) * groups < 512) B = (B / 2 + packs - 1) / packs * packs;
     // the fused kinds run two transforms between two waits on memory and gain more from a
     // further workgroup per CU: 320 x 250 x 180 fused FP32 714 us with 3 lines of 360 points
     // (18 KB), 625 with 2; FP64 1138 with 3, 1043 with 2 (24 KB), 1072 with 1
@@ -2004,10 +2004,11 @@ struct fm_batch_s {
 
 namespace {
 
-// Workgroups from which a one-launch group takes the largest tiles: two per CU.  64 FP64
-// solves of edges 32 ... 64 take 1046 us with them and 1317 us with the small tiles that a
-// plan of its own needs to fill the chip.
-constexpr int64_t kBatchTiles = 512;
+// Workgroups from which a one-launch group takes the largest tiles: two per CU, or fewer where
+// the small tiles, which a plan of its own needs to fill the chip, are that many more.  64
+// FP64 solves of edges 32 ... 64 take 1046 us with the large and 1317 us with the small tiles;
+// 8 of 48^3 (pass 2: 440 workgroups or 2304) 59 and 69, but 4 (220 or 1152) 49 and 44.
+constexpr int64_t kBatchTiles = 512, kBatchFewTiles = 128, kBatchSmallTiles = 1280;
 
 // The descriptor of pass ps of a plan in such a group.
 const fm::PassDesc& batch_tile(const fm_plan_s* p, int ps) {
@@ -2090,13 +2091,20 @@ int build_batch(int count, const fm_plan* plans, const void* const* rhs_dev, voi
     fm::PassDesc* hd = reinterpret_cast<fm::PassDesc*>(host->data() + g.off_desc);
     int* hp = reinterpret_cast<int*>(host->data() + g.off_pref);
     int acc = 0, mx = 0;
-    // a group that fills the chip with the largest tiles takes those
-    int64_t large = 0;
-    for (int j = 0; j < g.count; ++j) large += batch_tile(plans[order[g.first + j]], g.pass).tiles;
+    // a group that fills the chip with the largest tiles takes those, and two or more passes
+    // of the runtime-length kernel in any case (its tile of few points costs about as much as
+    // a whole one: 64 solves of 24 x 20 x 18 724 us with the plans' own tiles, 122 with the
+    // large ones; 4 of 36 x 40 x 30 118 and 67)
+    int64_t large = 0, small = 0;
+    for (int j = 0; j < g.count; ++j) {
+      large += batch_tile(plans[order[g.first + j]], g.pass).tiles;
+      small += all[5 * (size_t)order[g.first + j] + g.pass].tiles;
+    }
+    const bool wide = large >= kBatchTiles || (large >= kBatchFewTiles && small >= kBatchSmallTiles);
     for (int j = 0; j < g.count; ++j) {
       const int i = order[g.first + j];
       hd[j] = all[5 * (size_t)i + g.pass];
-      if (g.single < 0 && large >= kBatchTiles) {
+      if (g.single < 0 && (wide || (hd[j].rt_n && g.count > 1))) {
         const fm::PassDesc own = hd[j];
         hd[j] = batch_tile(plans[i], g.pass);
         hd[j].in = own.in;
@@ -2573,19 +2581,36 @@ bool retile(const fm_plan_s* p, int i, int bmax, int mode, fm::PassDesc* out) {
 extern "C++" {
 namespace {
 
+// Pass i in the runtime-length kernel with the planner's tile for a batch, of at most bmax
+// lines; false if it has none.
+bool retile_rt_batch(const fm_plan_s* p, int i, int bmax, fm::PassDesc* out) {
+  fm::PassDesc d = p->pass[i];
+  const bool fused_curl = i == 2 && p->kind != FM_POISSON;
+  const int64_t sizes_in[5] = {p->Vu, p->V1, p->V2, p->vec2 ? 2 * p->V2 : p->V2, p->V1};
+  const int64_t sizes_out[5] = {p->V1, p->V2, p->V2, p->V1, p->Vu};
+  if (choose_rt_tile(&d, p->elem, fused_curl ? 3 : 1, d.nb, bmax, false, false)) return false;
+  d.tiles = ((d.nb + d.B - 1) / d.B) * d.nc * (fused_curl ? 1 : d.ncomp);
+  set_magics(&d);
+  if (!pass_in_bounds(d, sizes_in[i], sizes_out[i], p->elem)) return false;
+  *out = d;
+  return true;
+}
+
 // The largest tiles of the passes that one-launch batches hold.  Two real lines share an
 // FFT, so a batch equals the single solves bitwise only where both tiles pair the same
-// lines: even ones.
+// lines: even ones, or all lines of the pass.
 void set_batch_tiles(fm_plan_s* p) {
   for (int i = 0; i < 5; ++i) {
     const fm::PassDesc& d = p->pass[i];
-    if (d.wave || d.rt_n) continue;
-    const bool pairs = d.gather != fm::G_CPLX;
-    if (pairs && d.B % 2) continue;
+    if (d.wave) continue;
+    auto alike = [&](const fm::PassDesc& t) { return d.gather == fm::G_CPLX || t.B % 2 == 0 || t.B >= t.nb; };
+    auto large = [&](int bmax, fm::PassDesc* t) {
+      return d.rt_n ? retile_rt_batch(p, i, bmax, t) : retile(p, i, bmax, 2, t);
+    };
     fm::PassDesc t;
-    if (!retile(p, i, 64, 2, &t)) continue;
-    if (pairs && t.B % 2 && (t.B == 1 || !retile(p, i, t.B - 1, 2, &t))) continue;
-    if (t.B > d.B && !(pairs && t.B % 2)) p->batch_pass[i] = t;
+    if (!alike(d) || !large(64, &t)) continue;
+    if (!alike(t) && (t.B == 1 || !large(t.B - 1, &t))) continue;
+    if (t.B > d.B && alike(t)) p->batch_pass[i] = t;
   }
 }
 
