@@ -474,8 +474,10 @@ bool set_rt(fm::PassDesc* d, size_t elem, int comps, int B) {
   if (comps * d->M > kRtLongestTile) return false;
   const RtLds t = rt_lds(*d, B, elem, comps);
   if (B < 1 || t.total > (size_t)fm::kMaxLds) return false;
-  int radix[fm::kRtStages];
-  const int n = fm::rt_schedule(d->M, radix);
+  int radix[fm::kRtStages], prod = 1;
+  for (int i = 0; i < d->rt_n; ++i) prod *= radix[i] = d->rt_radix[i];
+  // (a descriptor tiled again keeps its schedule: the search takes some 25 us)
+  const int n = d->rt_n > 0 && prod == d->M ? d->rt_n : fm::rt_schedule(d->M, radix);
   if (n < 1) return false;
   d->rt_n = n;
   int ns = 1;
@@ -1358,7 +1360,8 @@ bool packed_wave(const fm::PassDesc& d, int64_t lines) {
 //   * fused passes of 512 and more tiles: FP32 complex and curl lines (a factor 3; the others
 //     run per wavefront) 0.94-1.23; FP64 curl lines of 128 points and more 0.99-1.30; packed
 //     real lines, FP32 to 256 points (not 192: 0.62) 1.04-1.10, FP64 below 128 0.95-1.19 (at 128
-//     0.83); FP32 real-to-real to 256 points with no factor 3 (those 0.53-0.73) 1.02-1.14.
+//     0.83); FP32 real-to-real to 256 points with no factor 3 (those 0.53-0.73) 1.02-1.14 (not
+//     the semi-unbounded ones, half of zeros: 0.97, 192 x 64 x 192 nodes).
 int lds_table_mode(const fm::PassDesc& d, size_t elem) {
   if (d.rt_n) return -1;
   const int M = d.M, tiles = d.tiles;
@@ -1376,7 +1379,7 @@ int lds_table_mode(const fm::PassDesc& d, size_t elem) {
     case fm::K_F_C2C: return f32 && tiles >= 512 ? 1 : -1;
     case fm::K_F_CURL: return (f32 || M >= 128) && tiles >= 512 ? 1 : -1;
     case fm::K_F_R2C: return (f32 ? M <= 256 && M != 192 : M < 128) && tiles >= 512 ? 1 : -1;
-    case fm::K_F_R2R: return f32 && !three && M <= 256 && tiles >= 512 ? 1 : -1;
+    case fm::K_F_R2R: return f32 && !three && M <= 256 && 2 * d.in_n > d.r2r.nh + 2 && tiles >= 512 ? 1 : -1;
     default: return -1;
   }
 }
