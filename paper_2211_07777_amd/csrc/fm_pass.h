@@ -241,10 +241,15 @@ constexpr int wave_stage_count(int M, int E = kWaveValues) {
 constexpr int wave_tw_size(int M, int E = kWaveValues) {
   return wave_tw_offset(M, wave_stage_count(M, E), E);
 }
-// lines one wavefront holds (0 for lengths the per-wavefront kernels do not serve)
 // Post-twiddles of a plain real-to-real pass there: 2M entries of the 4M table, or M + 1 (an
 // even number, for the alignment of what follows) in the half form.
 constexpr int wave_post(int M, bool half) { return half ? M + 2 : 2 * M; }
+// Input values per thread of the plain per-wavefront kernel's register stage: B in_n / kThreads,
+// with in_n <= M + 1 where a tile has one line per FFT line (a node-centred periodic line keeps
+// its duplicate end point) and where two share it packed (R2C) or in the half form; and
+// in_n <= M / 2 + 1 in the packed half spectra and in symmetric extensions.
+constexpr int wave_plain_values(bool whole_pairs, int E) { return whole_pairs ? 2 * E + 1 : E + 1; }
+// lines one wavefront holds (0 for lengths the per-wavefront kernels do not serve)
 constexpr int wave_lines(int M, int E = kWaveValues) { return wave_length(M, E) ? 64 / (M / E) : 0; }
 
 // Lengths with compile-time kernels (other lengths use the runtime-length kernel).

@@ -645,7 +645,7 @@ size_t wave_plain_tab_bytes(const fm::PassDesc& d, int E, size_t elem) {
 
 // Input values per thread of the plain per-wavefront kernel's register stage.
 int wave_plain_u(const fm::PassDesc& d, int E) {
-  return d.gather == fm::G_REAL2 || d.gather == fm::G_R2R ? 2 * E + 1 : E + 1;
+  return fm::wave_plain_values(d.gather == fm::G_REAL2 || (d.gather == fm::G_R2R && d.r2r.half), E);
 }
 
 bool wave_capable(const fm::PassDesc& d, size_t elem) {

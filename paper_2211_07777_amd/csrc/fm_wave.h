@@ -363,10 +363,7 @@ struct WavePlain {
   static constexpr bool CIN = in_cplx_of(KIND);
   using In = typename std::conditional<CIN, cpx<T>, T>::type;
   static constexpr int REGION = L * LS * (CIN ? 1 : 2);   // a wavefront's LDS, in In units
-  // input values per thread: B in_n / kThreads with in_n <= M + 1 (a node-centred periodic
-  // line keeps its duplicate end point), or M / 2 + 1 for the packed half spectra and
-  // real-to-real lines
-  static constexpr int U = KIND == K_R2C || HALF ? 2 * E + 1 : E + 1;
+  static constexpr int U = wave_plain_values(KIND == K_R2C || HALF, E);  // input values per thread
   static constexpr int NTW = wave_tw_size(M, E);          // stage twiddles
   static constexpr int NPOST = KIND == K_R2R ? wave_post(M, HALF) : 0;  // real-to-real post-twiddles
   static constexpr int NSLOT = KIND == K_R2R ? M : 0;     // real-to-real gather slots
