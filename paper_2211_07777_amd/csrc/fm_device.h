@@ -385,9 +385,8 @@ __device__ __forceinline__ void stages_ct(cpx<T>* buf, int ls, int F, P stw, Loa
 // `keep` outputs of each line are written (the rest are cropped by the caller and never
 // read).
 template <typename T, int MC, int S, class P, class Load>
-__device__ __forceinline__ void fft_lines(cpx<T>* buf, int ls, int F, const PassDesc& d, P stw,
-                                          Load& load0, int keep = 1 << 30) {
-  (void)d;
+__device__ __forceinline__ void fft_lines(cpx<T>* buf, int ls, int F, P stw, Load& load0,
+                                          int keep = 1 << 30) {
   stages_ct<T, MC, S, 0, 1>(buf, ls, F, stw, load0, keep, NoSink{});
 }
 
@@ -639,14 +638,6 @@ __device__ __forceinline__ int fold_index(int k, int M) {
   return k < r ? k : r;
 }
 
-template <typename T>
-__device__ __forceinline__ T signed_wave(int k, int M, T dw) {
-  // wavenumber of DFT mode k of length M; the Nyquist mode differentiates to 0
-  if (2 * k == M) return T(0);
-  const int ks = (2 * k > M) ? k - M : k;
-  return dw * T(ks);
-}
-
 // u_hat = G i (w x f_hat) at one spectral point (Sec. V), in place.  The wavenumbers of
 // the b and c directions (physical axes ab, ac) may be imaginary, i mb / i mc (symmetric
 // directions, GreenRef::csym_b / csym; their real parts are then 0): their terms
@@ -732,7 +723,7 @@ __device__ __forceinline__ void plain_store(const PassDesc& d, void* out, const 
                                             const cpx<T>* buf, P tw) {
   const int scatter = KIND == K_ANY ? d.scatter : scatter_of(KIND);
   const int nl = ti.nl;
-  const int M = MC > 1 ? MC : d.M;
+  constexpr int M = MC;
   const int ls = fft_line_stride(M);
   const int64_t out_off = ti.comp * d.out_s_comp + ti.c * d.out_s_c + ti.b0 * d.out_s_b;
   if (scatter == S_CPLX) {
@@ -788,7 +779,7 @@ __device__ __forceinline__ void plain_compute(const PassDesc& d, void* out, cons
   const int sign = KIND == K_ANY ? d.sign : (KIND == K_C2C_I || KIND == K_C2R ? +1 : -1);
   const int nl = ti.nl;
   const P tw = tb.tw;
-  const int M = MC > 1 ? MC : d.M;
+  constexpr int M = MC;
   const int ls = fft_line_stride(M);
   cpx<T>* buf = reinterpret_cast<cpx<T>*>(smem);
   const int64_t out_off = ti.comp * d.out_s_comp + ti.c * d.out_s_c + ti.b0 * d.out_s_b;
@@ -798,64 +789,60 @@ __device__ __forceinline__ void plain_compute(const PassDesc& d, void* out, cons
   const int F = (gather == G_CPLX) ? nl : (nl + 1) / 2;
   if constexpr (DIRECT && KIND == K_C2C_F) {
     GatherCplxG<T> g{gptr<cpx<T>>(gin), d.in_s_b, d.n_data};
-    fft_lines<T, MC, -1>(buf, ls, F, d, tb.stw, g);
+    fft_lines<T, MC, -1>(buf, ls, F, tb.stw, g);
   } else if constexpr (DIRECT && KIND == K_R2C) {
     GatherReal2G<T> g{gptr<T>(gin), d.in_s_b, d.n_data, nl};
-    fft_lines<T, MC, -1>(buf, ls, F, d, tb.stw, g);
+    fft_lines<T, MC, -1>(buf, ls, F, tb.stw, g);
   } else if (gather == G_CPLX) {
     GatherCplx<T> g{reinterpret_cast<const cpx<T>*>(smem), rs, d.n_data};
     // complex lines are written from their first out_n slots (cropped inverse)
     const int keep = scatter == S_CPLX ? min(d.out_n, M) : M;
-    if constexpr (MC > 1) {
-      if (scatter == S_CPLX && d.out_s_line == 1) {
-        // contiguous output lines: the last stage stores them directly
-        cpx<T>* o = reinterpret_cast<cpx<T>*>(out) + out_off;
-        const int64_t sb = d.out_s_b;
-        const int on = d.out_n;
-        auto sink = [o, sb, on](int l, int j, const cpx<T>& v) {
-          cpx<T>* r = o + l * sb;
-          r[j] = v;
-          if (j + MC < on) r[j + MC] = v;
-        };
-        if (sign < 0) stages_ct<T, MC, -1, 0, 1>(buf, ls, F, tb.stw, g, keep, sink);
-        else stages_ct<T, MC, +1, 0, 1>(buf, ls, F, tb.stw, g, keep, sink);
-        return;
-      }
+    if (scatter == S_CPLX && d.out_s_line == 1) {
+      // contiguous output lines: the last stage stores them directly
+      cpx<T>* o = reinterpret_cast<cpx<T>*>(out) + out_off;
+      const int64_t sb = d.out_s_b;
+      const int on = d.out_n;
+      auto sink = [o, sb, on](int l, int j, const cpx<T>& v) {
+        cpx<T>* r = o + l * sb;
+        r[j] = v;
+        if (j + MC < on) r[j + MC] = v;
+      };
+      if (sign < 0) stages_ct<T, MC, -1, 0, 1>(buf, ls, F, tb.stw, g, keep, sink);
+      else stages_ct<T, MC, +1, 0, 1>(buf, ls, F, tb.stw, g, keep, sink);
+      return;
     }
-    if (sign < 0) fft_lines<T, MC, -1>(buf, ls, F, d, tb.stw, g, keep);
-    else fft_lines<T, MC, +1>(buf, ls, F, d, tb.stw, g, keep);
+    if (sign < 0) fft_lines<T, MC, -1>(buf, ls, F, tb.stw, g, keep);
+    else fft_lines<T, MC, +1>(buf, ls, F, tb.stw, g, keep);
   } else if (gather == G_REAL2) {
     GatherReal2<T> g{reinterpret_cast<const T*>(smem), rs, d.n_data, nl};
-    fft_lines<T, MC, -1>(buf, ls, F, d, tb.stw, g);
+    fft_lines<T, MC, -1>(buf, ls, F, tb.stw, g);
   } else if (gather == G_HERM2) {
     GatherHerm2<T> g{reinterpret_cast<const cpx<T>*>(smem), rs, M, nl};
-    if constexpr (MC > 1) {
-      if (scatter == S_REAL2 && !d.has_fix && d.out_s_line == 1) {
-        // contiguous real output lines without fix-ups: FFT line f holds tile lines 2f
-        // (real part) and 2f + 1 (imaginary part); the last stage stores them directly
-        T* o = reinterpret_cast<T*>(out) + out_off;
-        const int64_t sb = d.out_s_b;
-        const int on = d.out_n;
-        auto sink = [o, sb, on, nl](int f, int j, const cpx<T>& v) {
-          T* r0 = o + (2 * f) * sb;
-          r0[j] = v.x;
-          if (j + MC < on) r0[j + MC] = v.x;
-          if (2 * f + 1 < nl) {
-            T* r1 = r0 + sb;
-            r1[j] = v.y;
-            if (j + MC < on) r1[j + MC] = v.y;
-          }
-        };
-        stages_ct<T, MC, +1, 0, 1>(buf, ls, F, tb.stw, g, min(on, M), sink);
-        return;
-      }
+    if (scatter == S_REAL2 && !d.has_fix && d.out_s_line == 1) {
+      // contiguous real output lines without fix-ups: FFT line f holds tile lines 2f
+      // (real part) and 2f + 1 (imaginary part); the last stage stores them directly
+      T* o = reinterpret_cast<T*>(out) + out_off;
+      const int64_t sb = d.out_s_b;
+      const int on = d.out_n;
+      auto sink = [o, sb, on, nl](int f, int j, const cpx<T>& v) {
+        T* r0 = o + (2 * f) * sb;
+        r0[j] = v.x;
+        if (j + MC < on) r0[j + MC] = v.x;
+        if (2 * f + 1 < nl) {
+          T* r1 = r0 + sb;
+          r1[j] = v.y;
+          if (j + MC < on) r1[j + MC] = v.y;
+        }
+      };
+      stages_ct<T, MC, +1, 0, 1>(buf, ls, F, tb.stw, g, min(on, M), sink);
+      return;
     }
-    fft_lines<T, MC, +1>(buf, ls, F, d, tb.stw, g, scatter == S_REAL2 ? min(d.out_n, M) : M);
+    fft_lines<T, MC, +1>(buf, ls, F, tb.stw, g, scatter == S_REAL2 ? min(d.out_n, M) : M);
   } else {
     // the first stage builds the symmetric extension as it reads the raw tile (every
     // read of a stage precedes its writes, so the raw tile may alias the FFT buffer)
     GatherR2R<T, P> g{reinterpret_cast<const T*>(smem + d.raw_off), rs, d.in_n, nl, d.r2r, tw};
-    fft_lines<T, MC, -1>(buf, ls, F, d, tb.stw, g);
+    fft_lines<T, MC, -1>(buf, ls, F, tb.stw, g);
   }
 
   // 3) write the lines into the output layout
@@ -872,7 +859,7 @@ __device__ __forceinline__ void fused_compute(const PassDesc& d, void* out, cons
   const bool curl = KIND == K_ANY ? (d.g.curl != 0) : (KIND == K_F_CURL);
   const int nl = ti.nl, b0 = ti.b0, c = ti.c, comp = ti.comp;  // curl: comp = 0
   const P tw = tb.tw;
-  const int M = MC > 1 ? MC : d.M;
+  constexpr int M = MC;
   const int ls = fft_line_stride(M);
   cpx<T>* buf = reinterpret_cast<cpx<T>*>(smem);
   const int rs = d.in_n + 1;
@@ -889,7 +876,7 @@ __device__ __forceinline__ void fused_compute(const PassDesc& d, void* out, cons
     {
       GatherR2R<T, P> g{reinterpret_cast<const T*>(smem + d.raw_off), rs, d.in_n, nl, d.r2r, tw};
       extend_r2r<T, MC>(buf, ls, F, M, g);
-      fft_lines<T, MC, -1>(buf, ls, F, d, tb.stw, lds);
+      fft_lines<T, MC, -1>(buf, ls, F, tb.stw, lds);
     }
     // spectrum (real) into its own LDS region (where the raw tile was), times the
     // Green's spectrum
@@ -909,7 +896,7 @@ __device__ __forceinline__ void fused_compute(const PassDesc& d, void* out, cons
     {
       GatherR2R<T, P> g{spec, ss, d.spec_n, nl, d.r2r2, tw};
       extend_r2r<T, MC>(buf, ls, F, M, g);
-      fft_lines<T, MC, -1>(buf, ls, F, d, tb.stw, lds);
+      fft_lines<T, MC, -1>(buf, ls, F, tb.stw, lds);
     }
     const int64_t out_off = comp * d.out_s_comp + c * d.out_s_c + b0 * d.out_s_b;
     auto val = [&](int l, int j) { return scatter_r2r<T>(buf, ls, d.r2r2, tw, l, j); };
@@ -922,7 +909,7 @@ __device__ __forceinline__ void fused_compute(const PassDesc& d, void* out, cons
     // ---- only DFT axis of the problem: two real lines per FFT
     const int F = (nl + 1) / 2;
     GatherReal2<T> g{reinterpret_cast<const T*>(smem), rs, d.n_data, nl};
-    fft_lines<T, MC, -1>(buf, ls, F, d, tb.stw, g);
+    fft_lines<T, MC, -1>(buf, ls, F, tb.stw, g);
     // The two packed lines have their own Green rows: split Z into the two Hermitian
     // spectra X1 = (Z_k + conj Z_{M-k})/2, X2 = (Z_k - conj Z_{M-k})/(2i), scale each
     // by its (real, even) row, and pack again as Y1 + i Y2.  One thread owns the pair
@@ -955,7 +942,7 @@ __device__ __forceinline__ void fused_compute(const PassDesc& d, void* out, cons
         });
     __syncthreads();
     auto lds = [buf, ls](int line, int idx) { return buf[line * ls + pad16(idx)]; };
-    fft_lines<T, MC, +1>(buf, ls, F, d, tb.stw, lds);
+    fft_lines<T, MC, +1>(buf, ls, F, tb.stw, lds);
     const int64_t out_off = comp * d.out_s_comp + c * d.out_s_c + b0 * d.out_s_b;
     auto val = [&](int l, int j) {
       const cpx<T> z = buf[(l >> 1) * ls + pad16(j < M ? j : j - M)];
@@ -970,7 +957,7 @@ __device__ __forceinline__ void fused_compute(const PassDesc& d, void* out, cons
   const int F = ncl * nl;
   {
     GatherCplx<T> g{reinterpret_cast<const cpx<T>*>(smem), rs, d.n_data};
-    fft_lines<T, MC, -1>(buf, ls, F, d, tb.stw, g);
+    fft_lines<T, MC, -1>(buf, ls, F, tb.stw, g);
   }
   if (!curl) {
     // the multiplication by the Green's spectrum is the first inverse stage's load
@@ -980,24 +967,22 @@ __device__ __forceinline__ void fused_compute(const PassDesc& d, void* out, cons
       const T g = gl[line * FL + fold_index(idx, fl)];
       return cpx<T>{z.x * g, z.y * g};
     };
-    if constexpr (MC > 1) {
-      if (d.out_s_line == 1) {
-        // contiguous output lines: the last inverse stage's lanes hold consecutive slots
-        // of a line, so they store to global memory directly (no LDS pass, no store loop)
-        cpx<T>* o = reinterpret_cast<cpx<T>*>(out) + comp * d.out_s_comp + c * d.out_s_c +
-                    b0 * d.out_s_b;
-        const int64_t sb = d.out_s_b;
-        const int on = d.out_n;
-        auto sink = [o, sb, on](int l, int j, const cpx<T>& v) {
-          cpx<T>* r = o + l * sb;
-          r[j] = v;
-          if (j + MC < on) r[j + MC] = v;  // periodic duplicate beyond one period
-        };
-        stages_ct<T, MC, +1, 0, 1>(buf, ls, F, tb.stw, lds_g, min(on, M), sink);
-        return;
-      }
+    if (d.out_s_line == 1) {
+      // contiguous output lines: the last inverse stage's lanes hold consecutive slots
+      // of a line, so they store to global memory directly (no LDS pass, no store loop)
+      cpx<T>* o = reinterpret_cast<cpx<T>*>(out) + comp * d.out_s_comp + c * d.out_s_c +
+                  b0 * d.out_s_b;
+      const int64_t sb = d.out_s_b;
+      const int on = d.out_n;
+      auto sink = [o, sb, on](int l, int j, const cpx<T>& v) {
+        cpx<T>* r = o + l * sb;
+        r[j] = v;
+        if (j + MC < on) r[j + MC] = v;  // periodic duplicate beyond one period
+      };
+      stages_ct<T, MC, +1, 0, 1>(buf, ls, F, tb.stw, lds_g, min(on, M), sink);
+      return;
     }
-    fft_lines<T, MC, +1>(buf, ls, F, d, tb.stw, lds_g, min(d.out_n, M));
+    fft_lines<T, MC, +1>(buf, ls, F, tb.stw, lds_g, min(d.out_n, M));
   } else {
     T wc, mc;
     curl_factor<T>(d.g.csym, curl_wave<T>(c, d.g.dtab_c), wc, mc);
@@ -1029,24 +1014,22 @@ __device__ __forceinline__ void fused_compute(const PassDesc& d, void* out, cons
         });
     __syncthreads();
     auto lds = [buf, ls](int line, int idx) { return buf[line * ls + pad16(idx)]; };
-    if constexpr (MC > 1) {
-      if (d.out_s_line == 1) {
-        // contiguous output lines: component q's line l (FFT line q nl + l) is stored
-        // by the last inverse stage directly
-        cpx<T>* o = reinterpret_cast<cpx<T>*>(out) + c * d.out_s_c + b0 * d.out_s_b;
-        const int64_t sb = d.out_s_b, sq = d.out_s_comp;
-        const int on = d.out_n;
-        auto sink = [o, sb, sq, on, nl](int line, int j, const cpx<T>& v) {
-          const int q = line >= 2 * nl ? 2 : (line >= nl ? 1 : 0);
-          cpx<T>* r = o + q * sq + (line - q * nl) * sb;
-          r[j] = v;
-          if (j + MC < on) r[j + MC] = v;
-        };
-        stages_ct<T, MC, +1, 0, 1>(buf, ls, F, tb.stw, lds, min(on, M), sink);
-        return;
-      }
+    if (d.out_s_line == 1) {
+      // contiguous output lines: component q's line l (FFT line q nl + l) is stored
+      // by the last inverse stage directly
+      cpx<T>* o = reinterpret_cast<cpx<T>*>(out) + c * d.out_s_c + b0 * d.out_s_b;
+      const int64_t sb = d.out_s_b, sq = d.out_s_comp;
+      const int on = d.out_n;
+      auto sink = [o, sb, sq, on, nl](int line, int j, const cpx<T>& v) {
+        const int q = line >= 2 * nl ? 2 : (line >= nl ? 1 : 0);
+        cpx<T>* r = o + q * sq + (line - q * nl) * sb;
+        r[j] = v;
+        if (j + MC < on) r[j + MC] = v;
+      };
+      stages_ct<T, MC, +1, 0, 1>(buf, ls, F, tb.stw, lds, min(on, M), sink);
+      return;
     }
-    fft_lines<T, MC, +1>(buf, ls, F, d, tb.stw, lds, min(d.out_n, M));
+    fft_lines<T, MC, +1>(buf, ls, F, tb.stw, lds, min(d.out_n, M));
   }
   for (int q = 0; q < ncl; ++q) {
     const int cc = curl ? q : comp;
@@ -1348,7 +1331,7 @@ __device__ __forceinline__ void run_single(const PassDesc& d, const void* in, vo
     if (tile < 0) return;
     if (k > 0) __syncthreads();  // the previous tile's LDS reads are finished
     const TileIdx ti = tile_index(d, tile);
-    if constexpr (MC > 1 && (KIND == K_C2C_F || (KIND == K_R2C && MC <= 512))) {
+    if constexpr (KIND == K_C2C_F || (KIND == K_R2C && MC <= 512)) {
       if (d.in_s_line == 1) {
         // contiguous input lines: the first FFT stage reads them from global memory
         // (measured slower for real-to-complex lines of 1024 and more, which keep the
