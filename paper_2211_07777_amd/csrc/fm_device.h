@@ -1314,9 +1314,8 @@ __device__ __forceinline__ void run_pipelined(const PassDesc& d, const void* in,
   }
 }
 
-// One tile per workgroup (runtime lengths, long FP64 lines, and compile-time lengths
-// launched with one workgroup per tile): no register prefetch, tables read from global
-// memory.
+// One tile per workgroup: no register prefetch, tables read from global memory (the only
+// form of FP64 lines longer than kMaxFastLen64).
 template <typename T, int MC, int KIND>
 __device__ __forceinline__ void run_single(const PassDesc& d, const void* in, void* out,
                                            char* smem) {

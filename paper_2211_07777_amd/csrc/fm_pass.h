@@ -11,8 +11,7 @@ constexpr int kCurlThreads = 192;  // per-wavefront curl kernel: a wavefront per
 // Kernel length classes: a compile-time FFT length (> 1), or the runtime-length kernel.
 constexpr int kRuntime = 0;
 constexpr int kMaxFastLen64 = 2048;
-// Values per thread held across a radix stage for lines of length M (or kernel length
-// class M).  FP64 holds 8 (radices up to 8), so that a stage, its butterfly temporaries
+// Values per thread held across a radix stage of the LDS-tile kernel for lines of length M.  FP64 holds 8 (radices up to 8), so that a stage, its butterfly temporaries
 // and the persistent kernels' prefetch of the next tile stay in VGPRs; FP64 lines
 // longer than kMaxFastLen64 need 16 and run one tile per workgroup without prefetch.
 constexpr int elems_per_thread(int real_bytes, int M) {
@@ -338,7 +337,7 @@ struct PassDesc {
   int32_t wave_rs;          // plain passes: raw tile line stride, in input elements
   // Runtime-length kernel (fm_rt.h): its radix schedule and the multipliers of its index
   // divisions (rt_magic) by M / R and by the product of the earlier radices per stage, by
-  // M, by the padding M - n_data, and by spec_n; 0 stages: the in-place kernels.
+  // M, by the padding M - n_data, and by spec_n; 0 stages: another kernel.
   int32_t rt_n, rt_threads;
   int32_t rt_radix[kRtStages];
   uint32_t rt_mr[kRtStages], rt_ns[kRtStages];

@@ -259,7 +259,7 @@ struct fm_plan_s {
   fm::PassDesc pass[kPasses];
   bool force_rt[kPasses] = {};  // the pass needs the runtime-length kernel in the LDS-tile modes
   int line_M[kPasses] = {};  // FFT length of the pass in launch modes 0 to 5
-  const void* stw_plan[kPasses] = {};  // stage table of the planned kernel (null: runtime-length class)
+  const void* stw_plan[kPasses] = {};  // stage table of the planned kernel (null: runtime-length kernel)
   // FP64 passes outside the per-wavefront kernels with their largest tile, for one-launch batches (B = 0:
   // none), while the tiling is the planner's
   fm::PassDesc batch_pass[5] = {};
@@ -394,10 +394,11 @@ TileLds tile_lds(const fm::PassDesc& d, int B, size_t elem, int comps, bool fuse
   return t;
 }
 
-// FP32 one-launch batches and the FP32 fused real-to-real kernel of length 32 are off
-// in the library (an FP32 batched test faulted the GPU with no cause shown).  The CPU
-// emulation build of the device code (tests/emu) defines FM_FP32_ONE_LAUNCH to replay
-// those paths under the sanitizers.
+// FP32 one-launch batches and the FP32 fused real-to-real kernel of length 32 are off in
+// the library.  An FP32 batched test faulted the GPU; the cause (tile functions called as
+// functions, whose long branches overwrote their return address) is gone, and neither path
+// has run on a GPU since.  The CPU emulation build of the device code (tests/emu) defines
+// FM_FP32_ONE_LAUNCH to run both under the sanitizers.
 #ifdef FM_FP32_ONE_LAUNCH
 constexpr bool kFp32OneLaunch = true;
 #else
@@ -413,8 +414,7 @@ int runtime_form(const fm::PassDesc& d) {
 
 // Whether a pass runs in the compile-time-length kernel of its FFT length (else in the
 // runtime-length kernel).  FP32 fused real-to-real passes of length 32 are kept on the
-// runtime-length kernel: the compile-time one ran only in a test that faulted the GPU,
-// and nothing has shown it free of that fault.
+// runtime-length kernel (kFp32OneLaunch).
 bool compile_time_kernel(const fm::PassDesc& d, size_t elem) {
   if (d.force_rt || d.form_mode == 6 || !fm::is_fast_len(d.M)) return false;
   // N-point real-to-real forms are not the LDS-tile kernels', also where N itself has a
@@ -862,7 +862,7 @@ int make_tables_and_green(fm_plan_s* p, hipStream_t st, bool deferred) {
   }
   for (int i = 0; i < fm_plan_s::kPasses; ++i) p->pass[i].tw = p->tw[p->pass[i].M];
   // per-stage tables of the lengths with compile-time kernels; also of a pass planned in
-  // the runtime-length class that the tuner may move to the per-wavefront kernel (the
+  // the runtime-length kernel that the tuner may move to the per-wavefront kernel (the
   // table selects the compile-time class at launch, fm_plan_s::stw_plan keeps the planned
   // choice)
   for (int i = 0; i < fm_plan_s::kPasses; ++i) {
@@ -1403,7 +1403,7 @@ int lds_table_mode(const fm::PassDesc& d, size_t elem) {
 //   * packed DFT lines of 256 and 512 points in FP32 from 2^20 points: per wavefront
 //     (packed_wave);
 //   * the other passes: one tile per workgroup with tables from global memory (FP64 inverse
-//     DFT lines: in LDS), with at most the lines per tile that leave 256 workgroups to fill
+//     DFT lines: in LDS; and see lds_table_mode), with at most the lines per tile that leave 256 workgroups to fill
 //     the chip (FP64 64-point lines 6.4 / 7.7 on 65 k points; fused real-to-real 8.7 / 18.9
 //     on 32 k points, 89 / 180 on 3.3 M).
 // A choice is taken only if it is valid for this pass (pass_in_bounds on buffers of in_size
@@ -2513,7 +2513,9 @@ int fm_solve_batched(int count, const fm_plan* plans, const void* const* rhs_dev
 
 // Launch mode of a descriptor, as fm_plan_tiling reports it: 1 persistent with LDS
 // tables, 0 one tile per workgroup with LDS tables, 2 one tile per workgroup with global
-// tables (the only mode of the runtime-length and long FP64 kernels).
+// tables (the only mode of the runtime-length kernel and of FP64 lines longer than
+// kMaxFastLen64), 3 / 4 / 5 the per-wavefront kernels with 16 / 8 / 32 values per lane, 6 to 8
+// a form of its own (PassDesc::form_mode).
 int launch_mode(const fm::PassDesc& d, size_t elem) {
   if (d.form_mode) return d.form_mode;
   if (d.wave) return d.wave == 16 ? 3 : (d.wave == 8 ? 4 : 5);

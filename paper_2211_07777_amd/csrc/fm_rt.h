@@ -5,9 +5,9 @@
 // other, so a thread holds one butterfly at a time (not its whole share of the tile in
 // registers) and a stage ends in one barrier.  The index arithmetic divides by
 // host-made multipliers only, tile elements are walked by adding constant steps, and a
-// stage's twiddles lie in its own table, consecutive along k: with the integer divisions
-// and strided twiddle reads of the in-place form these lengths ran at 120-700 GB/s, bound
-// by address arithmetic.  All kinds share the radix stages (sign -1); an inverse
+// stage's twiddles lie in its own table, consecutive along k: with integer divisions and
+// strided twiddle reads these lengths ran at 120-700 GB/s, bound by address arithmetic.  The
+// three components of a curl share one buffer (rt_radix_in_place).  All kinds share the radix stages (sign -1); an inverse
 // transform is taken as the conjugate of the forward transform of the conjugate.
 #pragma once
 #include "fm_device.h"
