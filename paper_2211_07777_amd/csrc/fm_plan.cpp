@@ -1357,11 +1357,13 @@ bool packed_wave(const fm::PassDesc& d, int64_t lines) {
 //   * 256-point inverse complex lines in FP32, 1024 ... 4096 tiles: 1.04-1.15 (0.93 at 6192);
 //   * extensions of types II to IV in FP64, 384 points, 2048 and more tiles: 0.93-1.17, 768
 //     points, 16384 and more tiles: 1.05;
-//   * fused passes of 512 and more tiles: FP32 complex and curl lines (a factor 3; the others
-//     run per wavefront) 0.94-1.23; FP64 curl lines of 128 points and more 0.99-1.30; packed
-//     real lines, FP32 to 256 points (not 192: 0.62) 1.04-1.10, FP64 below 128 0.95-1.19 (at 128
-//     0.83); FP32 real-to-real to 256 points with no factor 3 (those 0.53-0.73) 1.02-1.14 (not
-//     the semi-unbounded ones, half of zeros: 0.97, 192 x 64 x 192 nodes).
+//   * fused passes of 512 and more tiles: FP32 complex and curl lines of 96 points and more (a
+//     factor 3; the others run per wavefront) 0.94-1.23 (48 points 0.73-0.93); FP64 curl lines of
+//     128 points and more 0.99-1.30; packed real lines, FP32 of 64 to 256 points (not 192: 0.62)
+//     0.96-1.14, FP64 of 64 points 1.14-1.23 and of 256, 2048 and more tiles, 0.98-1.12 (32
+//     points 0.78-0.89, 128 0.80-0.98); FP32 real-to-real of 128 and 256 points 1.01-1.14 (64
+//     points 0.82-0.94, a factor 3 0.53-1.04), but the semi-unbounded ones, half of zeros (192 x
+//     64 x 192 nodes 0.97).
 int lds_table_mode(const fm::PassDesc& d, size_t elem) {
   if (d.rt_n) return -1;
   const int M = d.M, tiles = d.tiles;
@@ -1376,10 +1378,12 @@ int lds_table_mode(const fm::PassDesc& d, size_t elem) {
     case fm::K_R2R:
       if (f32 || !three || !(d.r2r.a2 || d.r2r.b2)) return -1;
       return (M == 384 && tiles >= 2048) || (M == 768 && tiles >= 16384) ? 1 : -1;
-    case fm::K_F_C2C: return f32 && tiles >= 512 ? 1 : -1;
-    case fm::K_F_CURL: return (f32 || M >= 128) && tiles >= 512 ? 1 : -1;
-    case fm::K_F_R2C: return (f32 ? M <= 256 && M != 192 : M < 128) && tiles >= 512 ? 1 : -1;
-    case fm::K_F_R2R: return f32 && !three && M <= 256 && 2 * d.in_n > d.r2r.nh + 2 && tiles >= 512 ? 1 : -1;
+    case fm::K_F_C2C: return f32 && M >= 96 && tiles >= 512 ? 1 : -1;
+    case fm::K_F_CURL: return M >= (f32 ? 96 : 128) && tiles >= 512 ? 1 : -1;
+    case fm::K_F_R2C:
+      if (f32) return M >= 64 && M <= 256 && M != 192 && tiles >= 512 ? 1 : -1;
+      return (M == 64 && tiles >= 512) || (M == 256 && tiles >= 2048) ? 1 : -1;
+    case fm::K_F_R2R: return f32 && !three && M >= 128 && M <= 256 && 2 * d.in_n > d.r2r.nh + 2 && tiles >= 512 ? 1 : -1;
     default: return -1;
   }
 }

@@ -30,7 +30,12 @@ POIS, CURL = F.POISSON, F.BIOT_SAVART
     ([512, 128, 128], [P, P, P], F.F32, POIS, 1, {1: 4, 5: 4}),
     ([512, 256, 256], [P, P, P], F.F32, POIS, 1, {1: 1, 5: 4}),          # beyond the cache
     ([128, 128, 64], [D, E, P], F.F64, POIS, 3, {3: 1}),                 # fused packed lines
+    ([256, 200, 32], [D, E, P], F.F64, POIS, 1, {3: 2}),                 # 32 points
+    ([256, 200, 32], [D, E, P], F.F32, POIS, 1, {3: 2}),
+    ([256, 200, 48], [P, P, P], F.F32, POIS, 1, {3: 2}),                 # 48 points
+    ([256, 200, 48], [P, P, P], F.F32, CURL, 3, {3: 2}),
     ([128, 128, 64], [D, [1, 1], E], F.F32, POIS, 3, {3: 1}),            # fused real-to-real
+    ([256, 200, 32], [D, [1, 1], E], F.F32, POIS, 1, {3: 2}),            # 64 points
 ])
 def test_default_modes(n, bc, prec, kind, ncomp, modes):
     layout = F.NODE if bc == [U, P, D] else F.CELL
