@@ -1348,7 +1348,7 @@ bool packed_wave(const fm::PassDesc& d, int64_t lines) {
 // The launch mode with twiddle tables in LDS (1 persistent, 0 one tile per workgroup) of an
 // LDS-tile pass that is slower with them in global memory, else -1.  Per class of passes,
 // times with the tables in global memory over those of the persistent kernel (over mode 0
-// where it says so), 1552 passes of grids of edges 32 ... 384:
+// where it says so), 1800 passes of grids of edges 16 ... 500:
 //   * inverse lines with a factor 3 in FP32: complex, to 384 points, 0.82-1.17 (mode 0
 //     0.64-1.01); packed, 96 and 192 points, 0.94-1.34; packed, 384 and 768 points, 0.79-1.24
 //     (mode 0 0.67-1.10);

@@ -1,5 +1,6 @@
 """FP64 three-component lines of 1024 points (a 512-cell unbounded axis) per wavefront, with
-no, one or two symmetric axes (the default from 4096 lines on): against the FP64 oracle (1e-12 relative L-infinity, as every FP64 parity test), and against the runtime-length
+no, one or two symmetric axes (the default from 4096 lines on): against the FP64 oracle
+(1e-12 relative L-infinity, as every FP64 parity test), and against the runtime-length
 kernel on the same plan.  With a semi-unbounded axis beside the long unbounded one the
 Green's tables of library and oracle differ by up to 2e-12, whichever kernel runs (the
 runtime-length kernel's result is as far off), so that set is held to the second check."""
